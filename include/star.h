@@ -369,9 +369,10 @@ star_status star_score_variance(const star_load_params* p, const int32_t* cur_le
  *   moves: star_move [max_moves] device; moves[q] = q-th migration
  *         (req, src, tgt, gain) in execution order.  n_moves: int32 [1]
  *         device, the number made.
- * Cost: one classification-and-scoring pass over all N x n candidates and
- * one small update per allowed move (2 launches each; once the plan stops,
- * the remaining launches exit at once).
+ * Cost: one launch per allowed move (it executes the last pass's move and
+ * scores the next one over the candidates of O's requests), two more per
+ * call; once the plan stops, the remaining launches exit at once.  Besides
+ * two copies of the tables, the workspace holds 128 bytes per request.
  * ---------------------------------------------------------------------- */
 #define STAR_MAX_MOVES 4096
 

@@ -15,8 +15,7 @@ constexpr int kWave = 64;
 // here, and the calls that use a counter or the histogram leave it at zero).
 constexpr size_t kHdrErrorWord = 0;     // int32: sticky OR of STAR_DEV_* bits
 constexpr size_t kHdrVarTicket = 64;    // uint32: finished variance-scoring workgroups
-constexpr size_t kHdrPlanDone = 72;     // int32: the migration plan has stopped
-constexpr size_t kHdrPlanCount = 76;    // int32: moves made by the plan
+constexpr size_t kHdrPlanDone = 72;     // int32: 1 + the launch that ended the migration plan
 constexpr size_t kHdrScoreHist = 256;   // uint32[1024]: key-code histogram of the ranking
 static_assert(kHdrScoreHist + 1024 * 4 <= STAR_WS_HEADER_BYTES, "header holds the histogram");
 // uint32 arrival counters of the calls whose workgroups meet through a

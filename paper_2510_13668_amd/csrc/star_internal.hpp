@@ -140,8 +140,12 @@ hipError_t launch_variance(const star_load_params& p, const VarPlan& pl, const i
                            hipStream_t stream);
 
 struct PlanPlan {
-    VarPlan v;
-    size_t now_off = 0, total = 0;
+    VarPlan v;              // copy 0 of the tables
+    int blocks = 0;         // scoring workgroups of a pass
+    int chunks = 0, chunk_len = 0;   // request chunks of the current loads
+    size_t qt1_off = 0, lt1_off = 0;             // copy 1 of the tables
+    size_t now_off[2] = {0, 0}, part_off[2] = {0, 0};
+    size_t wsum_off = 0, nowp_off = 0, req_off = 0, total = 0;
 };
 PlanPlan plan_plan(const star_plan_params& p);
 hipError_t launch_plan(const star_plan_params& p, const PlanPlan& pl, const int32_t* cur,

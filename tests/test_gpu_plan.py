@@ -120,6 +120,25 @@ def test_workload_plans(name, moves):
     assert len(gpu["moves"]) == moves
 
 
+@pytest.mark.parametrize("N,n,b,K,moves,cur_hi,kw", [
+    (1, 2, 1, 1, 3, 50, {}),                                # one request, one bucket
+    (17, 2, 1, 3, 40, 50, {}),                              # requests that move again; stops early
+    (255, 6, 4, 12, 1, 4000, {}),                           # one move: first and last launch only
+    (3841, 16, 8, 130, 9, 4000, {}),                        # a ragged last run of requests
+    (61441, 3, 1, 5, 6, 4000, {}),                          # two rounds of requests per workgroup
+    (700, 530, 2, 4, 3, 4000, dict(theta=(1, 4))),         # more instances than threads
+    (300, 5, 64, 64, 12, 2**31 - 1, dict(mem_rule=1)),      # terms beyond the short products
+    (200, 7, 64, 40, 12, 4000, dict(theta=(3, 2))),         # theta above one
+    (200, 7, 64, 40, 12, 4000, dict(theta=(3, 2), u_rule=1)),
+])
+def test_plan_dispatch_edges(N, n, b, K, moves, cur_hi, kw):
+    """Sizes where the passes' layout can go wrong (one workgroup, ragged and
+    repeated rounds, more instances than threads, long products)."""
+    rng = np.random.default_rng(N + n)
+    cur, rem, inst = _crowded(rng, N, n, b, K, cur_hi=cur_hi)
+    _check(cur, rem, inst, synth.bucket_weights(K), n, b, K, moves, "edges", **kw)
+
+
 def test_rebalance_scan_plan_properties():
     """32768 requests on 64 instances: four moves, each checked on its own."""
     wl = synth.WORKLOADS["rebalance_scan"]
