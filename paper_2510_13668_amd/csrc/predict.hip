@@ -6,17 +6,19 @@
 // the continuous-prediction smoothing of Section 4.3 and integerisation.
 //
 // Kernel 1 (gemm1_splitk): Z1 partials = H W1^T over a K-slice, on MFMA
-//   (32x32 blocks), 128 bytes of K per LDS row (64 bf16 / 32 fp32),
-//   double-buffered LDS fed by register-staged 16-byte global loads, split-K
-//   so that small batches still fill the CUs.  Tile shapes: 64x64 on 4
-//   waves, 128x128 on 8 or 4 waves, 256x256 on 8 waves; a cost model picks
-//   one per product.  Partials are fp32, reduced later in a fixed order
+//   (32x32 blocks), 64 bytes of K per row and step (32 bf16 / 16 fp32)
+//   through a ring of LDS slots filled by direct global-to-LDS loads, split-K
+//   so that small batches still fill the CUs.  Tile shapes: 64x64 and 128x64
+//   on 4 waves, 128x128 and 256x256 on 8 waves; a cost model picks one per
+//   product.  Partials are fp32, reduced later in a fixed order
 //   (deterministic results).
 // Kernel 2 (head): 4 rows per workgroup (many workgroups, so the split-K
 //   partial reads have plenty of loads in flight), 16 for large batches:
 //   fixed-order split-K reduction, bias, activation, the bin GEMM (bf16 MFMA
 //   16x16x32 on a hi/lo split of a1, or fp32 FMA), softmax, expectation,
 //   EMA, round-half-even, clamp.
+#include <type_traits>
+
 #include "star_common.hpp"
 #include "star_internal.hpp"
 
@@ -25,25 +27,16 @@ namespace star {
 // ---------------------------------------------------------------------------
 // GEMM1
 // ---------------------------------------------------------------------------
-constexpr int G1_KBYTES = 128;                 // bytes of K per LDS row
-constexpr int G1_ROW = G1_KBYTES + 16;         // padded LDS row (bytes)
-constexpr int G1_CPR = G1_KBYTES / 16;         // 16-byte chunks per row
-// K-tiles of global loads in flight ahead of the multiply: three for the
-// 128 x 128 shape (one 8-wave workgroup per CU), two for the 64 x 64 one,
-// which runs two workgroups per CU that share the CU's load path (measured:
-// deeper register staging only lengthens each workgroup there).
-constexpr int G1_STAGES_BIG = 3;
-constexpr int G1_STAGES_SMALL = 2;
-constexpr int G1_STAGES_MID = 2;
-constexpr int G1_STAGES_WIDE = 2;
-constexpr int G1_WIDE_MIN_TILES = 1024;   // 128 x 128 tiles from which G1Wide replaces G1Big
-constexpr int G1_STAGES_HUGE = 1;
-constexpr int G1_HUGE_MIN_TILES = 256;    // 256 x 256 tiles (no split) from which G1Huge is used
-
-template <int kElemBytes> struct G1Elem {
-    static constexpr int BK = G1_KBYTES / kElemBytes;   // K elements per K-tile
-};
-
+// K is staged through LDS in steps of 128 bytes of every row (64 bf16, 32
+// fp32; 64 bytes in the 256 x 256 tile), by direct global-to-LDS loads into a
+// ring of NS slots: NS - 1 steps of loads are in flight and none of them
+// holds registers.  A slot's rows are packed, and chunk c (16 bytes) of row r
+// lies at position c ^ (r / 2 % 8) (64-byte rows: c ^ (r / 4 % 4)), so that
+// the 16 rows that a fragment read touches at a time cover all the banks.
+// The permutation is made by the loads' addresses: a wave's load fills 1 KiB
+// of LDS in lane order, 8 or 16 rows.  128 bytes are a whole cache line:
+// loads alone, from a cold L2, ran at 37.6 bytes per cycle and CU with such
+// rows and at 26.4 with half lines (1024 x 512 x 4096, 128 x 64 tiles).
 // Map blockIdx to a logical tile index so that consecutive logical indices
 // run on the same XCD (workgroups are dealt round-robin over the 8 XCDs):
 // logical neighbours share operand rows and hence that XCD's L2.
@@ -54,462 +47,352 @@ __device__ inline int xcd_logical_block(int bid, int nblk) {
 }
 
 // Tile shape of the split-K product: BM x BN outputs per workgroup, WM x WN
-// waves, each wave a (BM/WM) x (BN/WN) slab of 32 x 32 matrix-core blocks.
-template <int kBM, int kBN, int kWM, int kWN>
+// waves, each wave a (BM/WM) x (BN/WN) slab of 32 x 32 matrix-core blocks; a
+// ring of NS slots of STEP bytes per row; kAlt: the two halves of the waves
+// alternate (see g1_mainloop).
+template <int kBM, int kBN, int kWM, int kWN, int kStep, int kNS, bool kAlternate>
 struct G1Shape {
-    static constexpr int BM = kBM, BN = kBN, WM = kWM, WN = kWN;
-    static constexpr int THREADS = 64 * WM * WN;
+    static constexpr int BM = kBM, BN = kBN, WM = kWM, WN = kWN, STEP = kStep, NS = kNS;
+    static constexpr bool kAlt = kAlternate;
+    static constexpr int WAVES = WM * WN, THREADS = 64 * WAVES;
     static constexpr int MI = BM / WM / 32, NJ = BN / WN / 32;
-    static constexpr int CA = BM * G1_KBYTES / 16 / THREADS;   // 16-byte chunks per thread, A
-    static constexpr int CB = BN * G1_KBYTES / 16 / THREADS;   // ... and W
-    static constexpr int LDS_A = BM * G1_ROW, LDS_B = BN * G1_ROW;
-    static constexpr int OUT_ROW = BN + 8;     // floats per LDS row of the output tile
-    static_assert(MI >= 1 && NJ >= 1 && CA >= 1 && CB >= 1, "shape");
-    // the output tile goes out through LDS when it fits the operand buffers,
-    // else straight from the accumulators
-    static constexpr bool LDS_EPI = BM * OUT_ROW * 4 <= 2 * (LDS_A + LDS_B);
-};
-using G1Big = G1Shape<128, 128, 4, 2>;     // 8 waves, 32 x 64 slabs
-using G1Small = G1Shape<64, 64, 2, 2>;     // 4 waves, 32 x 32 slabs
-// 8 waves, 32 x 32 slabs of a 128 x 64 tile, for products of at most 128
-// rows: twice G1Big's tiles along N, so half its K-splits fill the chip, and
-// the partials written and read back halve.  The regression head's first
-// layer (2048 x 3584) went from 22.7 to 20.4 us per call at one row and
-// from 26.4 to 23.3 us at ten.  With several row tiles the cost model would
-// also pick it, but there it measured slower (the regression head's first
-// layer at 1024 rows: 29.3 against 33.9 us), so it is offered only here.
-using G1Mid = G1Shape<128, 64, 4, 2>;
-// 4 waves, 64 x 64 slabs: twice the matrix-core work per LDS byte of G1Big,
-// at half its waves per workgroup; it wins once every CU has several
-// workgroups queued (measured: 580 against 786 us for 32768 x 1024 x 8192)
-using G1Wide = G1Shape<128, 128, 2, 2>;
-// 8 waves, 64 x 128 slabs of a 256 x 256 tile: four times G1Big's matrix-core
-// work per byte loaded, one workgroup per CU (147 KiB of LDS); one K-tile in
-// flight keeps it within 256 registers.  For products with hundreds of such
-// tiles (measured at 32768 x 1024 x 8192: 511-715 us per call, 570 us on
-// average over 70 calls, 39% of peak, the matrix cores busy half the time).
-using G1Huge = G1Shape<256, 256, 4, 2>;
-
-// One K-tile of both operands staged in registers (constant indices only,
-// so the stages stay in VGPRs).
-template <class SH>
-struct G1Stage {
-    uint4 a[SH::CA], b[SH::CB];
-};
-
-struct G1Ctx {
-    const char* A;
-    const char* W;
-    int M, N, tm, tn, tid, threads, bm, bn;
-    int64_t row_bytes;
-};
-
-// Loads are unconditional (addresses clamped into the operands) so the
-// compiler can count them and wait only for the stage it is about to store;
-// out-of-range values are zeroed when they are written to LDS.
-__device__ __forceinline__ uint4 g1_load(const G1Ctx& c, const char* base, int rows, int row0,
-                                         int p, int64_t kb) {
-    const int ch = c.tid + p * c.threads;
-    const int row = row0 + ch / G1_CPR;
-    const int64_t off = kb + (ch % G1_CPR) * 16;
-    const int64_t ko = off < c.row_bytes ? off : 0;
-    return *(const uint4*)(base + (int64_t)(row < rows ? row : rows - 1) * c.row_bytes + ko);
-}
-
-template <class SH>
-__device__ __forceinline__ void g1_load_stage(const G1Ctx& c, int kt, G1Stage<SH>& s) {
-    const int64_t kb = (int64_t)kt * G1_KBYTES;
-    const int ra = c.tm * SH::BM, rb = c.tn * SH::BN;
-#pragma unroll
-    for (int p = 0; p < SH::CA; ++p) s.a[p] = g1_load(c, c.A, c.M, ra, p, kb);
-#pragma unroll
-    for (int p = 0; p < SH::CB; ++p) s.b[p] = g1_load(c, c.W, c.N, rb, p, kb);
-}
-
-__device__ __forceinline__ void g1_store_chunk(const G1Ctx& c, char* l, int p, int64_t kb,
-                                               int row0, int rows, uint4 v) {
-    const int ch = c.tid + p * c.threads;
-    const int row = ch / G1_CPR;
-    const int cb = (ch % G1_CPR) * 16;
-    // bitwise masks, not a select of uint4 structs (which would go through memory)
-    const uint32_t m = (kb + cb < c.row_bytes && row0 + row < rows) ? 0xFFFFFFFFu : 0u;
-    *(uint4*)(l + row * G1_ROW + cb) = make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
-}
-
-template <class SH>
-__device__ __forceinline__ void g1_store_stage(const G1Ctx& c, char* la, char* lb, int kt,
-                                               const G1Stage<SH>& s) {
-    const int64_t kb = (int64_t)kt * G1_KBYTES;
-#pragma unroll
-    for (int p = 0; p < SH::CA; ++p) g1_store_chunk(c, la, p, kb, c.tm * SH::BM, c.M, s.a[p]);
-#pragma unroll
-    for (int p = 0; p < SH::CB; ++p) g1_store_chunk(c, lb, p, kb, c.tn * SH::BN, c.N, s.b[p]);
-}
-
-// A wave multiplies its (32 MI) x (32 NJ) slab: rows wm * 32 MI..,
-// columns wn * 32 NJ..
-template <int kElemBytes, class SH>
-__device__ __forceinline__ void g1_compute(const char* la, const char* lb, int wm, int wn,
-                                           int lane, f32x16 (&acc)[SH::MI][SH::NJ]) {
-    constexpr int BK = G1Elem<kElemBytes>::BK;
-    constexpr int MI = SH::MI, NJ = SH::NJ;
-    const int r32 = lane & 31;
-    const int khalf = lane >> 5;   // which half of the MFMA's K slice this lane feeds
-    constexpr int KK = BK / 16;
-    if constexpr (kElemBytes == 2 && (MI + NJ) * KK <= 12) {
-        // every fragment of the K-tile is read from LDS first, so the wave
-        // waits for LDS once per K-tile and then issues its MFMAs back to back
-        bf16x8_t a[KK][MI], b[KK][NJ];
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            const int koff = (kk * 16 + khalf * 8) * 2;
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-                a[kk][i] = __builtin_bit_cast(bf16x8_t, *(const bf16x8*)(la + (wm * 32 * MI + i * 32 + r32) * G1_ROW + koff));
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                b[kk][j] = __builtin_bit_cast(bf16x8_t, *(const bf16x8*)(lb + (wn * 32 * NJ + j * 32 + r32) * G1_ROW + koff));
-        }
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][i], b[kk][j], acc[i][j], 0, 0, 0);
-        // keep that order: the scheduler would otherwise pair reads with
-        // MFMAs to save registers and wait for LDS once per pair
-        __builtin_amdgcn_sched_group_barrier(0x100, (MI + NJ) * KK, 0);   // LDS reads
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NJ * KK, 0);     // MFMAs
-    } else if constexpr (kElemBytes == 2) {
-        // v_mfma_f32_32x32x16_bf16: lane feeds row (lane%32), k = 8*(lane/32)..+7
-#pragma unroll
-        for (int kk = 0; kk < BK / 16; ++kk) {
-            const int koff = (kk * 16 + khalf * 8) * 2;
-            bf16x8_t a[MI], b[NJ];
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-                a[i] = __builtin_bit_cast(bf16x8_t, *(const bf16x8*)(la + (wm * 32 * MI + i * 32 + r32) * G1_ROW + koff));
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                b[j] = __builtin_bit_cast(bf16x8_t, *(const bf16x8*)(lb + (wn * 32 * NJ + j * 32 + r32) * G1_ROW + koff));
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    } else {
-        // v_mfma_f32_32x32x2_f32: lane feeds row (lane%32), k = lane/32
-#pragma unroll
-        for (int kk = 0; kk < BK / 2; ++kk) {
-            const int koff = (kk * 2 + khalf) * 4;
-            float a[MI], b[NJ];
-#pragma unroll
-            for (int i = 0; i < MI; ++i) a[i] = *(const float*)(la + (wm * 32 * MI + i * 32 + r32) * G1_ROW + koff);
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(lb + (wn * 32 * NJ + j * 32 + r32) * G1_ROW + koff);
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
+    static constexpr int CPR = STEP / 16;           // 16-byte chunks per row
+    static constexpr int RPL = 64 / CPR;            // rows of one wave's load
+    static constexpr int KK = CPR / 2;              // products of a step, in K
+    static constexpr int CA = BM * CPR / THREADS;   // 16-byte chunks per thread, A
+    static constexpr int CB = BN * CPR / THREADS;   // ... and W
+    static constexpr int SLOT = (BM + BN) * STEP, LDS = NS * SLOT;
+    // position of chunk c of row r (see above)
+    __device__ static constexpr int pos(int c, int r) {
+        return STEP == 128 ? c ^ ((r >> 1) & 7) : c ^ ((r >> 2) & 3);
     }
-}
+    static_assert(STEP == 128 || STEP == 64, "whole or half cache lines");
+    static_assert(MI >= 1 && NJ >= 1 && CA >= 1 && CB >= 1, "shape");
+    static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
+};
+// Whole star_predict calls (us, captured graphs) with these rings, against
+// the register-staged loop and padded LDS rows that they replace (before):
+//   1024 x 512 x 4096  18.7 -> 15.8     4096 x 512 x 5120  44.0 -> 36.6
+//   777 x 512 x 3584   17.2 -> 14.8     512 x 512 x 4096   15.0 -> 13.3
+// Three slots: with four, the LDS of one workgroup less on a CU, 15.9, 36.6,
+// 14.8 and 13.4, and 118 against 94.6 for 8 overlapped batches.  With six
+// slots of half cache lines: 16.9, 39.9, 15.6 and 13.5.
+using G1Small = G1Shape<64, 64, 2, 2, 128, 3, false>;     // 48 KiB of LDS: three per CU
+using G1Mid = G1Shape<128, 64, 2, 2, 128, 3, false>;      // 72 KiB: two per CU
+using G1Big = G1Shape<128, 128, 2, 4, 128, 3, false>;     // 96 KiB, 64 x 32 slabs
+// 128 x 64 slabs, all 160 KiB of LDS: a third of G1Big's LDS reads per
+// product.  Its two wave groups alternate (528 us without, 464-537 with; the
+// register-staged loop took 550-609).
+// What bounds it at 32768 x 1024 x 8192: the operand loads alone take 387 us
+// and the MFMAs alone 340 us (at 1.77 GHz: the matrix cores run into the
+// card's power limit; the whole kernel runs at 1.5-1.7 GHz).
+using G1Huge = G1Shape<256, 256, 2, 4, 64, 5, true>;
+constexpr int G1_HUGE_MIN_TILES = 256;    // 256 x 256 tiles (no split) from which G1Huge is used
 
-// One pipeline step: stage s holds tile i; write it to LDS buffer i % 2,
-// barrier, refill s with tile i + NS (or re-read tile i -- a cache hit --
-// past the end, so that every step issues exactly one stage of loads), and
-// multiply buffer i % 2.  A buffer is rewritten two steps after its last
-// use, and every thread has passed the intervening barrier only after
-// finishing that use.
-template <int kElemBytes, int NS, class SH>
-__device__ __forceinline__ void g1_step(const G1Ctx& c, char (*lds)[SH::LDS_A + SH::LDS_B],
-                                        int kt0, int nk, int i, G1Stage<SH>& s, int wm, int wn,
-                                        int lane, f32x16 (&acc)[SH::MI][SH::NJ]) {
-    const int buf = i & 1;
-    // scheduling fences keep each phase in place: otherwise the compiler
-    // hoists the next stage's masking into the multiply, which then waits
-    // for loads issued only one step earlier
-    __builtin_amdgcn_sched_barrier(0);
-    g1_store_stage<SH>(c, lds[buf], lds[buf] + SH::LDS_A, kt0 + i, s);
-    __syncthreads();
-    g1_load_stage<SH>(c, kt0 + (i + NS < nk ? i + NS : i), s);
-    __builtin_amdgcn_sched_barrier(0);
-    g1_compute<kElemBytes, SH>(lds[buf], lds[buf] + SH::LDS_A, wm, wn, lane, acc);
-}
-
-// The work of one workgroup of the split-K product: tile (tm, tn), K-tiles
-// [kt0, kt1).  Workgroups are dealt to the XCDs round-robin; the logical
+// The work of one workgroup of the split-K product: tile (tm, tn), K-steps
+// [kt0, kt0 + nk), and the last, partial step of a K that is no whole number
+// of steps.  Workgroups are dealt to the XCDs round-robin; the logical
 // order puts one K-slice of neighbouring tiles on each XCD.
 struct G1Work {
-    int split, tile, tm, tn, kt0, nk;
+    int split, tm, tn, kt0, nk;
+    int tail;                 // bytes of K in the partial step (0: none)
 };
-__device__ inline G1Work g1_work(int splits, int tiles_n, int ktiles, int bid, int nblocks) {
+template <class SH>
+__device__ inline G1Work g1_work(int splits, int tiles_n, int64_t row_bytes, int bid,
+                                 int nblocks) {
     G1Work w;
     const int logical = xcd_logical_block(bid, nblocks);
     const int tiles = nblocks / splits;
     w.split = logical / tiles;
-    w.tile = logical % tiles;
-    w.tm = w.tile / tiles_n;
-    w.tn = w.tile % tiles_n;
-    w.kt0 = (int)((int64_t)w.split * ktiles / splits);
-    const int kt1 = (int)((int64_t)(w.split + 1) * ktiles / splits);
-    w.nk = kt1 - w.kt0;
+    const int tile = logical % tiles;
+    w.tm = tile / tiles_n;
+    w.tn = tile % tiles_n;
+    // at most 2^27 steps (K < 2^31) and 16 splits: 32-bit products, whose
+    // divisions are short (64-bit ones took 400 instructions before the first load)
+    const uint32_t steps = (uint32_t)(row_bytes / SH::STEP);
+    w.kt0 = (int)((uint32_t)w.split * steps / (uint32_t)splits);
+    w.nk = (int)((uint32_t)(w.split + 1) * steps / (uint32_t)splits) - w.kt0;
+    w.tail = w.split == splits - 1 ? (int)(row_bytes % SH::STEP) : 0;
     return w;
 }
 
-// Main loop of one workgroup's product: NS K-tiles of global loads are in
-// flight ahead of the tile being multiplied (register staging, two LDS
-// buffers, one barrier per K-tile).  acc receives this wave's slab.
-template <int kElemBytes, int NS, class SH>
-__device__ __forceinline__ void g1_mainloop_edge(const G1Ctx& c, const G1Work& w,
-                                                 char (*lds)[SH::LDS_A + SH::LDS_B], int wm,
-                                                 int wn, int lane, f32x16 (&acc)[SH::MI][SH::NJ]) {
-    const int nk = w.nk, kt0 = w.kt0;
-    if (nk > 0) {
-        G1Stage<SH> st[NS];
-#pragma unroll
-        for (int u = 0; u < NS; ++u) g1_load_stage<SH>(c, kt0 + (u < nk ? u : 0), st[u]);
-        int i = 0;
-        for (; i + NS <= nk; i += NS) {
-#pragma unroll
-            for (int u = 0; u < NS; ++u)
-                g1_step<kElemBytes, NS, SH>(c, lds, kt0, nk, i + u, st[u], wm, wn, lane, acc);
-        }
-#pragma unroll
-        for (int u = 0; u < NS - 1; ++u)
-            if (i + u < nk) g1_step<kElemBytes, NS, SH>(c, lds, kt0, nk, i + u, st[u], wm, wn, lane, acc);
-    }
+// 16 bytes per lane from global memory to LDS (wave-uniform base + 16 lane)
+__device__ __forceinline__ void g1_load_lds(const char* g, char* l) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                     (__attribute__((address_space(3))) void*)l, 16, 0, 0);
 }
-
-// The same for a tile wholly inside the product whose K is a whole number
-// of K-tiles: nothing to clamp or mask.  Each thread's row offsets (32-bit,
-// the operands are under 4 GiB) and LDS offsets are computed once; per
-// K-tile only the uniform base pointer moves, so the loads take the
-// scalar-base form and the loop carries no per-element masks.
-template <class SH>
-struct G1Fast {
-    uint32_t ga[SH::CA], gb[SH::CB];          // global byte offsets within a K-tile column
-    uint32_t la[SH::CA], lb[SH::CB];          // LDS byte offsets
-};
-typedef uint32_t g1u4 __attribute__((ext_vector_type(4)));
-template <class SH>
-struct G1FStage {                             // one K-tile of both operands in registers
-    g1u4 a[SH::CA], b[SH::CB];
-};
-
-template <class SH>
-__device__ __forceinline__ void g1f_load(const G1Ctx& c, const G1Fast<SH>& f, int kt,
-                                         G1FStage<SH>& st) {
-    const char* pa = c.A + (int64_t)kt * G1_KBYTES;
-    const char* pb = c.W + (int64_t)kt * G1_KBYTES;
-#pragma unroll
-    for (int p = 0; p < SH::CA; ++p) st.a[p] = *(const g1u4*)(pa + f.ga[p]);
-#pragma unroll
-    for (int p = 0; p < SH::CB; ++p) st.b[p] = *(const g1u4*)(pb + f.gb[p]);
+// at most kN of this wave's vector-memory operations outstanding
+template <int kN>
+__device__ __forceinline__ void g1_wait_vm() {
+    static_assert(kN < 64, "vmcnt has six bits");
+    __builtin_amdgcn_s_waitcnt((kN & 15) | (7 << 4) | (15 << 8) | ((kN >> 4) << 14));
 }
-
-template <int kElemBytes, int NS, class SH>
-__device__ __forceinline__ void g1f_step(const G1Ctx& c, const G1Fast<SH>& f,
-                                         char (*lds)[SH::LDS_A + SH::LDS_B], int kt0, int nk,
-                                         int i, G1FStage<SH>& st, int wm, int wn, int lane,
-                                         f32x16 (&acc)[SH::MI][SH::NJ]) {
-    char* l = lds[i & 1];
+__device__ __forceinline__ void g1_wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+// A barrier that waits for no memory operation (the waits are explicit); the
+// compiler moves nothing across it.
+__device__ __forceinline__ void g1_barrier() {
     __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int p = 0; p < SH::CA; ++p) *(g1u4*)(l + f.la[p]) = st.a[p];
-#pragma unroll
-    for (int p = 0; p < SH::CB; ++p) *(g1u4*)(l + f.lb[p]) = st.b[p];
-    __syncthreads();
-    g1f_load<SH>(c, f, kt0 + (i + NS < nk ? i + NS : i), st);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    g1_compute<kElemBytes, SH>(l, l + SH::LDS_A, wm, wn, lane, acc);
 }
 
-template <int kElemBytes, int NS, class SH>
-__device__ __forceinline__ void g1_mainloop_interior(const G1Ctx& c, const G1Work& w,
-                                                     char (*lds)[SH::LDS_A + SH::LDS_B], int wm,
-                                                     int wn, int lane,
-                                                     f32x16 (&acc)[SH::MI][SH::NJ]) {
-    G1Fast<SH> f;
+// A wave's fragments of one step: of each of its rows, the 16-byte chunks 2 kk
+// + lane / 32 of K.  pos[kk]: where they lie in a row.
+template <class SH>
+struct G1Frag {
+    u32x4 a[SH::KK][SH::MI], b[SH::KK][SH::NJ];
+};
+template <class SH>
+__device__ __forceinline__ void g1_read_frag(const char* slot, int offa, int offb,
+                                             const int (&pos)[SH::KK], G1Frag<SH>& f) {
 #pragma unroll
-    for (int p = 0; p < SH::CA; ++p) {
-        const int ch = c.tid + p * c.threads;
-        f.ga[p] = (uint32_t)((c.tm * SH::BM + ch / G1_CPR) * c.row_bytes + (ch % G1_CPR) * 16);
-        f.la[p] = (uint32_t)((ch / G1_CPR) * G1_ROW + (ch % G1_CPR) * 16);
+    for (int kk = 0; kk < SH::KK; ++kk) {
+#pragma unroll
+        for (int i = 0; i < SH::MI; ++i)
+            f.a[kk][i] = *(const u32x4*)(slot + offa + i * 32 * SH::STEP + pos[kk]);
+#pragma unroll
+        for (int j = 0; j < SH::NJ; ++j)
+            f.b[kk][j] = *(const u32x4*)(slot + offb + j * 32 * SH::STEP + pos[kk]);
     }
+}
+// bf16: v_mfma_f32_32x32x16_bf16, lane feeds row lane % 32, the 8 k of its
+// chunk.  fp32: v_mfma_f32_32x32x2_f32 takes one k of each half wave, so
+// element e of the two chunks makes one product.
+template <int kElemBytes, class SH>
+__device__ __forceinline__ void g1_mfma(const G1Frag<SH>& f, f32x16 (&acc)[SH::MI][SH::NJ]) {
 #pragma unroll
-    for (int p = 0; p < SH::CB; ++p) {
-        const int ch = c.tid + p * c.threads;
-        f.gb[p] = (uint32_t)((c.tn * SH::BN + ch / G1_CPR) * c.row_bytes + (ch % G1_CPR) * 16);
-        f.lb[p] = (uint32_t)(SH::LDS_A + (ch / G1_CPR) * G1_ROW + (ch % G1_CPR) * 16);
-    }
-    const int nk = w.nk, kt0 = w.kt0;
-    if (nk > 0) {
-        G1FStage<SH> st[NS];
+    for (int kk = 0; kk < SH::KK; ++kk) {
+        if constexpr (kElemBytes == 2) {
 #pragma unroll
-        for (int u = 0; u < NS; ++u) g1f_load<SH>(c, f, kt0 + (u < nk ? u : 0), st[u]);
-        int i = 0;
-        for (; i + NS <= nk; i += NS) {
+            for (int i = 0; i < SH::MI; ++i)
 #pragma unroll
-            for (int u = 0; u < NS; ++u)
-                g1f_step<kElemBytes, NS, SH>(c, f, lds, kt0, nk, i + u, st[u], wm, wn, lane, acc);
+                for (int j = 0; j < SH::NJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        __builtin_bit_cast(bf16x8_t, f.a[kk][i]),
+                        __builtin_bit_cast(bf16x8_t, f.b[kk][j]), acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < SH::MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < SH::NJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                            __uint_as_float(f.a[kk][i][e]), __uint_as_float(f.b[kk][j][e]),
+                            acc[i][j], 0, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < NS - 1; ++u)
-            if (i + u < nk)
-                g1f_step<kElemBytes, NS, SH>(c, f, lds, kt0, nk, i + u, st[u], wm, wn, lane, acc);
     }
 }
 
-template <int kElemBytes, int NS, class SH>
-__device__ __forceinline__ void g1_mainloop(const char* A, const char* W, int M, int N, int Kd,
-                                            const G1Work& w, char (*lds)[SH::LDS_A + SH::LDS_B],
+// Steps i + kJ, i + kJ + 1, .. of the last NS - 1, as far as nk: fewer and
+// fewer loads stay outstanding.
+template <int NS, int L, int kJ, class Step>
+__device__ __forceinline__ void g1_drain(Step& step, int i, int nk) {
+    if constexpr (kJ < NS - 1) {
+        if (i + kJ >= nk) return;
+        step(std::integral_constant<int, kJ < NS - 3 ? (NS - 3 - kJ) * L : 0>{}, -1);
+        g1_drain<NS, L, kJ + 1>(step, i, nk);
+    }
+}
+
+// Main loop of one workgroup's product; acc receives this wave's slab.  Rows
+// past M or N repeat the last one (their outputs are never stored).
+//
+// Step i reads the wave's fragments of slot i % NS, requests step i + NS - 1
+// into the slot of step i - 1, waits for its fragments and for its own loads
+// of step i + 1, passes one barrier and multiplies.  The barrier publishes
+// step i + 1 to all waves, and shows that all have read slot i % NS, which
+// step i + 1 refills.
+//
+// kAlt: the upper half of the waves (one per SIMD, like the lower half) runs
+// one barrier behind, and a second barrier follows the products, so that one
+// half multiplies while the other reads.  The same two conditions hold half a
+// step later: the upper half passes the barrier after its waits of step i
+// before the lower half reads step i + 1, and the lower half requests a slot
+// only after the upper half has read it.
+template <int kElemBytes, class SH>
+__device__ __forceinline__ void g1_mainloop(const char* __restrict__ A,
+                                            const char* __restrict__ W, int M, int N,
+                                            int64_t row_bytes, const G1Work& w, char* lds,
                                             f32x16 (&acc)[SH::MI][SH::NJ]) {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wid = tid >> 6;
+    constexpr int CA = SH::CA, CB = SH::CB, L = CA + CB, NS = SH::NS;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wid / SH::WN, wn = wid % SH::WN;
-    G1Ctx c;
-    c.A = A; c.W = W; c.M = M; c.N = N; c.tm = w.tm; c.tn = w.tn; c.tid = tid;
-    c.threads = SH::THREADS; c.bm = SH::BM; c.bn = SH::BN;
-    c.row_bytes = (int64_t)Kd * kElemBytes;
+    const int r32 = lane & 31, khalf = lane >> 5;
 #pragma unroll
     for (int i = 0; i < SH::MI; ++i)
 #pragma unroll
         for (int j = 0; j < SH::NJ; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    // uniform over the workgroup: rows and columns in range, K whole tiles,
-    // and both operands addressable with 32-bit offsets
-    const bool interior = (w.tm + 1) * SH::BM <= M && (w.tn + 1) * SH::BN <= N &&
-                          c.row_bytes % G1_KBYTES == 0 &&
-                          (int64_t)M * c.row_bytes < ((int64_t)1 << 32) &&
-                          (int64_t)N * c.row_bytes < ((int64_t)1 << 32);
-    if (interior)
-        g1_mainloop_interior<kElemBytes, NS, SH>(c, w, lds, wm, wn, lane, acc);
-    else
-        g1_mainloop_edge<kElemBytes, NS, SH>(c, w, lds, wm, wn, lane, acc);
+
+    // this lane's 16 bytes of each of its wave's loads: load p fills the RPL
+    // rows from (p WAVES + wid) RPL on.  The chunk is the one that belongs at
+    // the lane's position; it is the same for every p, because RPL WAVES is a
+    // multiple of the permutation's period.
+    static_assert(SH::RPL * SH::WAVES % 16 == 0, "one permutation per lane");
+    const int lrow = wid * SH::RPL + lane / SH::CPR;
+    const int chunk = SH::pos(lane % SH::CPR, lrow) * 16;
+    const char* pa[CA];
+    const char* pb[CB];
+#pragma unroll
+    for (int p = 0; p < CA; ++p) {
+        const int row = w.tm * SH::BM + p * SH::WAVES * SH::RPL + lrow;
+        pa[p] = A + (int64_t)(row < M ? row : M - 1) * row_bytes + chunk;
+    }
+#pragma unroll
+    for (int p = 0; p < CB; ++p) {
+        const int row = w.tn * SH::BN + p * SH::WAVES * SH::RPL + lrow;
+        pb[p] = W + (int64_t)(row < N ? row : N - 1) * row_bytes + chunk;
+    }
+    const int nk = w.nk;
+    char* const mine = lds + wid * 1024;      // the wave's first KiB of a slot
+    auto request = [&](int i, int slot) {
+        const int64_t kb = (int64_t)(w.kt0 + (i < nk ? i : nk - 1)) * SH::STEP;
+        char* l = mine + slot * SH::SLOT;
+#pragma unroll
+        for (int p = 0; p < CA; ++p) g1_load_lds(pa[p] + kb, l + p * SH::WAVES * 1024);
+#pragma unroll
+        for (int p = 0; p < CB; ++p)
+            g1_load_lds(pb[p] + kb, l + SH::BM * SH::STEP + p * SH::WAVES * 1024);
+    };
+    // the partial step, if any, is requested first and held in registers until
+    // the whole steps are done (its chunks past K read the row's start and are
+    // zeroed when they are written to LDS)
+    u32x4 ta[CA], tb[CB];
+    if (w.tail) {
+        const int64_t kb = chunk < w.tail ? (int64_t)(w.kt0 + nk) * SH::STEP : -(int64_t)chunk;
+#pragma unroll
+        for (int p = 0; p < CA; ++p) ta[p] = *(const u32x4*)(pa[p] + kb);
+#pragma unroll
+        for (int p = 0; p < CB; ++p) tb[p] = *(const u32x4*)(pb[p] + kb);
+    }
+
+    const int offa = (wm * 32 * SH::MI + r32) * SH::STEP;
+    const int offb = SH::BM * SH::STEP + (wn * 32 * SH::NJ + r32) * SH::STEP;
+    int pos[SH::KK];
+#pragma unroll
+    for (int kk = 0; kk < SH::KK; ++kk) pos[kk] = SH::pos(2 * kk + khalf, r32) * 16;
+    G1Frag<SH> f;
+    if (nk > 0) {
+        // requests of the first NS - 1 steps; fewer steps repeat the last one
+        // (a K-slice that short is all latency), so that the waits below hold
+#pragma unroll
+        for (int d = 0; d < NS - 1; ++d) request(d, d);
+        g1_wait_vm<(NS - 2) * L>();
+        g1_barrier();
+        const bool late = SH::kAlt && wid >= SH::WAVES / 2;
+        if (late) g1_barrier();
+        int slot = 0;
+        // one step; at most kOut of the wave's loads stay outstanding after it
+        auto step = [&](auto kOut, int next) {
+            __builtin_amdgcn_sched_barrier(0);
+            g1_read_frag<SH>(lds + slot * SH::SLOT, offa, offb, pos, f);
+            __builtin_amdgcn_sched_barrier(0);
+            if (next >= 0) request(next, slot == 0 ? NS - 1 : slot - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            g1_wait_lds();
+            g1_wait_vm<decltype(kOut)::value>();
+            g1_barrier();
+            if (SH::kAlt) __builtin_amdgcn_s_setprio(1);
+            g1_mfma<kElemBytes, SH>(f, acc);
+            if (SH::kAlt) {
+                __builtin_amdgcn_s_setprio(0);
+                g1_barrier();
+            }
+            slot = slot + 1 == NS ? 0 : slot + 1;
+        };
+        int i = 0;
+        for (; i + NS - 1 < nk; ++i)
+            step(std::integral_constant<int, (NS - 2) * L>{}, i + NS - 1);
+        // the last NS - 1 steps request nothing
+        g1_drain<NS, L, 0>(step, i, nk);
+        if (SH::kAlt && !late) g1_barrier();
+        g1_wait_vm<0>();          // repeated requests
+        g1_barrier();             // every wave has read its last fragments: the ring is free
+    }
+    if (w.tail) {
+        const uint32_t in = chunk < w.tail ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int p = 0; p < CA; ++p)
+            *(u32x4*)(mine + p * SH::WAVES * 1024 + lane * 16) = ta[p] & in;
+#pragma unroll
+        for (int p = 0; p < CB; ++p)
+            *(u32x4*)(mine + SH::BM * SH::STEP + p * SH::WAVES * 1024 + lane * 16) = tb[p] & in;
+        __syncthreads();
+        g1_read_frag<SH>(lds, offa, offb, pos, f);
+        g1_mfma<kElemBytes, SH>(f, acc);
+    }
 }
 
 // Split-K product P[split] = A[:, Ks] W[:, Ks]^T over one BM x BN tile: the
 // work of block `bid` of a grid of `nblocks` product blocks.
-template <int kElemBytes, int NS, class SH>
+template <int kElemBytes, class SH>
 __device__ __forceinline__ void gemm1_tile(const char* __restrict__ A, const char* __restrict__ W,
                                            float* __restrict__ P, int M, int N, int Kd,
-                                           int splits, int tiles_n, int ktiles, int bid,
-                                           int nblocks,
-                                           char (*lds)[SH::LDS_A + SH::LDS_B]) {
-    constexpr int MI = SH::MI, NJ = SH::NJ;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wid = tid >> 6;
+                                           int splits, int tiles_n, int bid, int nblocks,
+                                           char* lds) {
+    const int lane = threadIdx.x & 63;
+    const int wid = threadIdx.x >> 6;
     const int wm = wid / SH::WN, wn = wid % SH::WN;
-    const G1Work w = g1_work(splits, tiles_n, ktiles, bid, nblocks);
-    const int split = w.split, tm = w.tm, tn = w.tn;
-    f32x16 acc[MI][NJ];
-    g1_mainloop<kElemBytes, NS, SH>(A, W, M, N, Kd, w, lds, acc);
-    const int r32 = lane & 31;
-    const int khalf = lane >> 5;
-
-    // epilogue: the 32x32 accumulator layout (element v of lane l is row
-    // 8*(v/4) + 4*(l/32) + v%4, column l%32 of its block) goes through LDS
-    // (the operand buffers, free now) so that global stores are whole
-    // 16-byte row chunks.  LDS rows hold OUT_ROW floats (the padding puts
-    // the two 4-row halves of a store on disjoint banks).  Tiles too large
-    // for that store each accumulator element directly: 32 lanes write 128
-    // contiguous bytes of a row.
-    if constexpr (!SH::LDS_EPI) {
-        float* outd = P + (int64_t)split * M * N;
+    const int64_t row_bytes = (int64_t)Kd * kElemBytes;
+    const G1Work w = g1_work<SH>(splits, tiles_n, row_bytes, bid, nblocks);
+    f32x16 acc[SH::MI][SH::NJ];
+    g1_mainloop<kElemBytes, SH>(A, W, M, N, row_bytes, w, lds, acc);
+    // Element v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) +
+    // v % 4, column l % 32: a store covers 128 contiguous bytes of two rows.
+    // (Collecting rows in LDS first, for 16-byte stores, was slower: 9.9
+    // against 9.6 us at 1024 x 512 x 4096.)  The partials are written once
+    // and read once by the next kernel: non-temporal stores stream them out
+    // instead of leaving them dirty in L2 for the end-of-kernel writeback.
+    float* out = P + (int64_t)w.split * M * N;
+    const int r32 = lane & 31, khalf = lane >> 5;
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < SH::MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int gcol = tn * SH::BN + wn * 32 * NJ + j * 32 + r32;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int grow = tm * SH::BM + wm * 32 * MI + i * 32 + 8 * (v >> 2) +
-                                     4 * khalf + (v & 3);
-                    if (grow < M && gcol < N)
-                        __builtin_nontemporal_store(acc[i][j][v], &outd[(int64_t)grow * N + gcol]);
-                }
-            }
-        return;
-    }
-    __syncthreads();
-    float* otile = (float*)&lds[0][0];
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int col = wn * 32 * NJ + j * 32 + r32;
+        for (int j = 0; j < SH::NJ; ++j) {
+            const int gcol = w.tn * SH::BN + wn * 32 * SH::NJ + j * 32 + r32;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = wm * 32 * MI + i * 32 + 8 * (v >> 2) + 4 * khalf + (v & 3);
-                otile[row * SH::OUT_ROW + col] = acc[i][j][v];
+                const int grow = w.tm * SH::BM + wm * 32 * SH::MI + i * 32 + 8 * (v >> 2) +
+                                 4 * khalf + (v & 3);
+                if (grow < M && gcol < N)
+                    __builtin_nontemporal_store(acc[i][j][v], &out[(int64_t)grow * N + gcol]);
             }
         }
-    __syncthreads();
-    float* out = P + (int64_t)split * M * N;
-    constexpr int CH = SH::BM * SH::BN / 4;           // float4 chunks in the tile
-#pragma unroll
-    for (int it = 0; it < CH / SH::THREADS; ++it) {
-        const int ch = it * SH::THREADS + tid;
-        const int row = ch / (SH::BN / 4), c4 = ch % (SH::BN / 4);
-        const int grow = tm * SH::BM + row, gcol = tn * SH::BN + c4 * 4;
-        if (grow < M && gcol < N)                     // N % 4 == 0: chunks never straddle N
-            // partials are written once and read once by the next kernel:
-            // non-temporal stores stream them out instead of leaving them
-            // dirty in L2 for the end-of-kernel writeback (measured: 15.8 ->
-            // 12.8 us at 1024 x 512 x 4096 with four splits)
-            __builtin_nontemporal_store(*(const f32x4*)&otile[row * SH::OUT_ROW + c4 * 4],
-                                        (f32x4*)&out[(int64_t)grow * N + gcol]);
-    }
 }
 
-template <int kElemBytes, int NS, class SH>
+template <int kElemBytes, class SH>
 __global__ __launch_bounds__(SH::THREADS) void gemm1_splitk_kernel(
     const char* __restrict__ A, const char* __restrict__ W, float* __restrict__ P,
-    int M, int N, int Kd, int splits, int tiles_n, int ktiles) {
-    __shared__ __attribute__((aligned(16))) char lds[2][SH::LDS_A + SH::LDS_B];
-    gemm1_tile<kElemBytes, NS, SH>(A, W, P, M, N, Kd, splits, tiles_n, ktiles, blockIdx.x,
-                                   gridDim.x, lds);
+    int M, int N, int Kd, int splits, int tiles_n) {
+    __shared__ __attribute__((aligned(1024))) char lds[SH::LDS];
+    gemm1_tile<kElemBytes, SH>(A, W, P, M, N, Kd, splits, tiles_n, blockIdx.x, gridDim.x, lds);
 }
 
 // Launch of the split-K product with the plan's tile shape.
-template <int NS, class SH>
+template <class SH>
 static void launch_gemm_shape(const GemmPlan& g, bool bf16, const void* A, const void* W,
                               float* P, int M, int N, int K, hipStream_t stream) {
     const dim3 grid(g.tiles_m * g.tiles_n * g.splits);
     if (bf16)
-        hipLaunchKernelGGL((gemm1_splitk_kernel<2, NS, SH>), grid, dim3(SH::THREADS), 0, stream,
-                           (const char*)A, (const char*)W, P, M, N, K, g.splits, g.tiles_n,
-                           g.ktiles);
+        hipLaunchKernelGGL((gemm1_splitk_kernel<2, SH>), grid, dim3(SH::THREADS), 0, stream,
+                           (const char*)A, (const char*)W, P, M, N, K, g.splits, g.tiles_n);
     else
-        hipLaunchKernelGGL((gemm1_splitk_kernel<4, NS, SH>), grid, dim3(SH::THREADS), 0, stream,
-                           (const char*)A, (const char*)W, P, M, N, K, g.splits, g.tiles_n,
-                           g.ktiles);
+        hipLaunchKernelGGL((gemm1_splitk_kernel<4, SH>), grid, dim3(SH::THREADS), 0, stream,
+                           (const char*)A, (const char*)W, P, M, N, K, g.splits, g.tiles_n);
 }
 
 static hipError_t launch_gemm(const GemmPlan& g, bool bf16, const void* A, const void* W,
                               float* P, int M, int N, int K, hipStream_t stream) {
     switch (g.shape) {
-        case GemmPlan::kBig:
-            launch_gemm_shape<G1_STAGES_BIG, G1Big>(g, bf16, A, W, P, M, N, K, stream);
-            break;
-        case GemmPlan::kWide:
-            launch_gemm_shape<G1_STAGES_WIDE, G1Wide>(g, bf16, A, W, P, M, N, K, stream);
-            break;
-        case GemmPlan::kHuge:
-            launch_gemm_shape<G1_STAGES_HUGE, G1Huge>(g, bf16, A, W, P, M, N, K, stream);
-            break;
-        case GemmPlan::kMid:
-            launch_gemm_shape<G1_STAGES_MID, G1Mid>(g, bf16, A, W, P, M, N, K, stream);
-            break;
-        default:
-            launch_gemm_shape<G1_STAGES_SMALL, G1Small>(g, bf16, A, W, P, M, N, K, stream);
+        case GemmPlan::kBig: launch_gemm_shape<G1Big>(g, bf16, A, W, P, M, N, K, stream); break;
+        case GemmPlan::kHuge: launch_gemm_shape<G1Huge>(g, bf16, A, W, P, M, N, K, stream); break;
+        case GemmPlan::kMid: launch_gemm_shape<G1Mid>(g, bf16, A, W, P, M, N, K, stream); break;
+        default: launch_gemm_shape<G1Small>(g, bf16, A, W, P, M, N, K, stream);
     }
     return hipGetLastError();
 }
@@ -524,8 +407,8 @@ constexpr int HD_THREADS = 256;
 // float4 items per thread whose partial loads are in flight together: more
 // when there are few split-K planes (registers hold kS x batch float4)
 template <int kS> constexpr int hd_batch() { return kS == 1 ? 8 : kS == 2 ? 4 : 2; }
-// W2 fragments (K-steps of 32) a wave loads at a time, the first group at
-// kernel entry so that its latency overlaps the split-K reads.  A deep group
+// W2 fragments (16 bins x one K-step) a wave loads at a time, the first group
+// at kernel entry so that its latency overlaps the split-K reads.  A deep group
 // costs registers: past two workgroups per CU (more than 512 of them) the
 // shallow one, which keeps every workgroup resident, is faster (measured:
 // 54.9 -> 50.8 us per call at 4096 rows with two planes; at 1024 rows the
@@ -559,13 +442,34 @@ __device__ inline float apply_act(float x, int act) {
     return gelu_erf(x);
 }
 
+// K of one step of the second product: the 16-byte chunks of the four lane
+// groups (32 bf16, or 16 fp32)
+template <bool kBF16> constexpr int hd_step() { return kBF16 ? 32 : 16; }
+// LDS of the head: a1 (rows padded by 16 bytes against bank conflicts, K to
+// whole steps; the bf16 hi and lo parts, or fp32), then the four waves' shares
+// of the logits
+static constexpr size_t head_rows_lds(bool bf16, int m, int nb) {
+    const size_t step = bf16 ? 32 : 16;
+    const size_t mpad = (m + step - 1) / step * step;
+    const size_t a1 = bf16 ? 2 * HD_RB * (mpad + 8) * 2 : HD_RB * (mpad + 4) * 4;
+    return a1 + (HD_THREADS / 64) * HD_RB * (((size_t)nb + 15) / 16 * 16) * 4;
+}
+
 // kS = number of split-K partial planes (compile time, so that all of a
 // thread's partial loads are issued before the first is consumed).
 // kReg: the regression head's last two layers instead of the binned one
 // (the nb "bin logits" are the third layer's outputs, `bins` holds w4 and
 // phase 3 computes relu(z) . w4 + b4 in place of the softmax mean).
 // The head over rows [blk HD_RB, (blk + 1) HD_RB), its buffers in `smem`
-// (head_lds bytes).
+// (head_rows_lds bytes).
+//
+// A chain of latencies bounds it (1024 rows, 4 planes, 8 MiB read: 6.2-7.3
+// us; the fp32 head of 64 rows went from 8.6 to 6.8).  The partials, which
+// everything waits for, are requested before anything else.  In the second product each wave takes
+// a quarter of the K-steps for every bin: it then reads a quarter of a1 from
+// LDS, where a quarter of the bins per wave read all of it in every wave,
+// and its products of four bin blocks are independent.  The four shares are
+// summed in wave order.  The softmax reduces by DPP, not by LDS shuffles.
 template <bool kBF16, int kS, bool kReg, int kPF>
 __device__ __forceinline__ void head_rows(
     const float* __restrict__ P, int B, int m, int nb, const float* __restrict__ b1,
@@ -574,83 +478,101 @@ __device__ __forceinline__ void head_rows(
     float* __restrict__ expected, int32_t* __restrict__ rem_len, int len_max, float b4, int blk,
     char* smem) {
     constexpr int kBatch = hd_batch<kS>();
+    constexpr int kWaves = HD_THREADS / 64;
+    constexpr int kStep = hd_step<kBF16>();
+    constexpr int kPB = kPF < 4 ? kPF : 4;        // bin blocks of 16 at a time
+    constexpr int kPK = kPF / kPB;                // K-steps at a time
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wid = tid >> 6;
     const int row0 = blk * HD_RB;
-    const int mpad = (m + 31) & ~31;
-    const int astride = mpad + 8;                 // bf16 elements per LDS row
+    const int mpad = (m + kStep - 1) / kStep * kStep;
+    const int astride = mpad + (kBF16 ? 8 : 4);   // elements per LDS row
     const int nbpad = (nb + 15) & ~15;
 
     uint16_t* ahi = (uint16_t*)smem;
     uint16_t* alo = ahi + HD_RB * astride;
     float* a32 = (float*)smem;
-    float* z = kBF16 ? (float*)(alo + HD_RB * astride) : (float*)(a32 + HD_RB * m);
-
-    // 0) everything phases 2 and 3 read from global memory is requested now,
-    //    so that its latency overlaps the split-K reads
-    const int r16 = lane & 15;
-    const int kq = lane >> 4;
-    const int j0 = wid * 16 + r16;                // this lane's bin in the wave's first block
-    bf16x8 wf0[kPF];
-    if constexpr (kBF16) {
-        const uint16_t* W2 = (const uint16_t*)w2;
-        // Loads are unconditional (clamped indices) so none of them is waited
-        // for before it is used.  An out-of-range fragment reads W2[0, 0..7]:
-        // it only ever meets zero K-padding of a1 or lands in a column >= nb,
-        // which is discarded.
-#pragma unroll
-        for (int u = 0; u < kPF; ++u) {
-            const int k = u * 32 + kq * 8;
-            const bool in = j0 < nb && k < m;
-            wf0[u] = *(const bf16x8*)(W2 + (in ? (int64_t)j0 * m + k : 0));
-        }
-    }
-    float binv[4];                                // used only where lane + 64 i < nb
-#pragma unroll
-    for (int i = 0; i < 4; ++i) binv[i] = bins[lane + 64 * i < nb ? lane + 64 * i : nb - 1];
-    const float b2v = b2 ? b2[j0 < nb ? j0 : nb - 1] : 0.0f;
-    const int my_row = row0 + wid;                // the row this wave finishes in phase 3
-    const float ema_prev = (ema_alpha > 0.0f && !ema_init) ? ema_state[my_row < B ? my_row : B - 1] : 0.0f;
+    float* z = kBF16 ? (float*)(alo + HD_RB * astride) : a32 + HD_RB * astride;
 
     // 1) fixed-order split-K reduction, bias, activation (float4 items)
     const int m4 = m >> 2;
     const int items = HD_RB * m4;
     const int64_t plane4 = (int64_t)B * m4;
     const float4* P4 = (const float4*)P;
-    for (int base = 0; base < items; base += kBatch * HD_THREADS) {
-        float4 v[kBatch][kS];
-        float4 bv[kBatch];
-        int row[kBatch], c4[kBatch];
-        bool ok[kBatch];
+    f32x4 v[kBatch][kS], bv[kBatch];
+    int row[kBatch], c4[kBatch];
+    bool ok[kBatch];
+    auto load_items = [&](int base) {
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
-            const int e = base + i * HD_THREADS + tid;
-            row[i] = e / m4;
-            c4[i] = e - row[i] * m4;
-            ok[i] = e < items && row0 + row[i] < B;
+            const uint32_t e = base + i * HD_THREADS + tid;
+            row[i] = (int)(e / (uint32_t)m4);
+            c4[i] = (int)(e - (uint32_t)row[i] * (uint32_t)m4);
+            ok[i] = (int)e < items && row0 + row[i] < B;
             const int64_t off = ok[i] ? (int64_t)(row0 + row[i]) * m4 + c4[i] : 0;
 #pragma unroll
-            for (int q = 0; q < kS; ++q) {
+            for (int q = 0; q < kS; ++q)
                 // read once: streamed past L2 (non-temporal), so they do not
                 // evict the operands the next product reads
-                const f32x4 t = __builtin_nontemporal_load((const f32x4*)&P4[q * plane4 + off]);
-                v[i][q] = make_float4(t[0], t[1], t[2], t[3]);
-            }
-            bv[i] = b1 ? *(const float4*)(b1 + 4 * c4[i]) : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[i][q] = __builtin_nontemporal_load((const f32x4*)&P4[q * plane4 + off]);
+            bv[i] = b1 ? *(const f32x4*)(b1 + 4 * c4[i]) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    };
+    load_items(0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // everything phases 2 and 3 read from global memory is requested next, so
+    // that its latency overlaps the split-K reads.  A lane's fragment of bin
+    // block j and K-step u: the 16 bytes at W2[16 j + lane % 16][u kStep + (lane
+    // / 16) chunk].  Loads are unconditional (clamped indices) so none of them
+    // is waited for before it is used; columns past nb are discarded, K past
+    // m is zeroed (fp32) or meets a1's zero padding (bf16).
+    const int r16 = lane & 15;
+    const int kq = lane >> 4;
+    const int ksteps = mpad / kStep;
+    constexpr int kChunk = kBF16 ? 8 : 4;         // elements per fragment
+    u32x4 wf[kPK][kPB];
+    // K-steps s0 .. s0 + kPK - 1 of this wave (step s of it is s kWaves + wid)
+    auto load_w2 = [&](int s0, int j0) {
+#pragma unroll
+        for (int u = 0; u < kPK; ++u)
+#pragma unroll
+            for (int j = 0; j < kPB; ++j) {
+                const int bin = (j0 + j) * 16 + r16;
+                const int k = ((s0 + u) * kWaves + wid) * kStep + kq * kChunk;
+                const bool in = bin < nb && k < m;
+                const int64_t off = in ? (int64_t)bin * m + k : 0;
+                wf[u][j] = kBF16 ? *(const u32x4*)((const uint16_t*)w2 + off)
+                                 : *(const u32x4*)((const float*)w2 + off);
+                if (!kBF16) wf[u][j] &= in ? 0xFFFFFFFFu : 0u;
+            }
+    };
+    load_w2(0, 0);
+    float binv[4], b2v[4];                        // used only where lane + 64 i < nb
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = lane + 64 * i < nb ? lane + 64 * i : nb - 1;
+        binv[i] = bins[j];
+        b2v[i] = b2 ? b2[j] : 0.0f;
+    }
+    const int gr = row0 + wid;                    // the row this wave finishes in phase 3
+    const float ema_prev =
+        (ema_alpha > 0.0f && !ema_init) ? ema_state[gr < B ? gr : B - 1] : 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+
+    for (int base = 0; base < items; base += kBatch * HD_THREADS) {
+        if (base > 0) load_items(base);
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
             const int e = base + i * HD_THREADS + tid;
             if (e >= items) continue;
-            float4 sum = v[i][0];
+            f32x4 sum = v[i][0];
 #pragma unroll
-            for (int q = 1; q < kS; ++q) {
-                sum.x += v[i][q].x; sum.y += v[i][q].y; sum.z += v[i][q].z; sum.w += v[i][q].w;
-            }
-            float a[4] = {sum.x + bv[i].x, sum.y + bv[i].y, sum.z + bv[i].z, sum.w + bv[i].w};
+            for (int q = 1; q < kS; ++q) sum += v[i][q];
+            float a[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a[j] = ok[i] ? apply_act(a[j], act) : 0.0f;
+            for (int j = 0; j < 4; ++j) a[j] = ok[i] ? apply_act(sum[j] + bv[i][j], act) : 0.0f;
             if constexpr (kBF16) {
                 uint32_t h0, l0, h1, l1;
                 split_bf16x2(a[0], a[1], h0, l0);
@@ -659,139 +581,133 @@ __device__ __forceinline__ void head_rows(
                 *(uint2*)(ahi + o) = make_uint2(h0, h1);
                 *(uint2*)(alo + o) = make_uint2(l0, l1);
             } else {
-                *(float4*)(a32 + row[i] * m + 4 * c4[i]) = make_float4(a[0], a[1], a[2], a[3]);
+                *(float4*)(a32 + row[i] * astride + 4 * c4[i]) = make_float4(a[0], a[1], a[2], a[3]);
             }
         }
     }
-    if constexpr (kBF16) {      // zero K padding [m, mpad)
+    if (mpad > m) {             // zero K padding [m, mpad)
         for (int e = tid; e < HD_RB * (mpad - m); e += HD_THREADS) {
             const int r = e / (mpad - m), u = m + e % (mpad - m);
-            ahi[r * astride + u] = 0;
-            alo[r * astride + u] = 0;
+            if constexpr (kBF16) {
+                ahi[r * astride + u] = 0;
+                alo[r * astride + u] = 0;
+            } else {
+                a32[r * astride + u] = 0.0f;
+            }
         }
     }
     __syncthreads();
 
-    // 2) bin logits
-    if constexpr (kBF16) {
-        // v_mfma_f32_16x16x32_bf16: lane feeds row (lane%16), k = 8*(lane/16)..+7;
-        // accumulator element v of lane l is row 4*(l/16)+v, column l%16.  Only
-        // rows < HD_RB are real; the other A rows are fed as zeros.
-        const uint16_t* W2 = (const uint16_t*)w2;
-        const bool arow = r16 < HD_RB;
-        for (int nblk = wid; nblk * 16 < nb; nblk += HD_THREADS / 64) {
-            const int j = nblk * 16 + r16;
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int kb = 0; kb < mpad; kb += 32 * kPF) {
-                bf16x8 wf[kPF];
-                if (nblk == wid && kb == 0) {
+    // 2) bin logits: lane feeds A row lane % 16 and B row (bin) lane % 16, the
+    // chunk of K of group lane / 16; accumulator element v of lane l is row
+    // 4 (l / 16) + v, column l % 16.  Only the first HD_RB rows are stored,
+    // so the others repeat them (rows of a product do not mix).
+    const int aoff = (r16 % HD_RB) * astride + kq * kChunk;
+    const int nblocks = nbpad / 16;
+    for (int j0 = 0; j0 < nblocks; j0 += kPB) {
+        f32x4 acc[kPB];
 #pragma unroll
-                    for (int u = 0; u < kPF; ++u) wf[u] = wf0[u];
+        for (int j = 0; j < kPB; ++j) acc[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int s0 = 0; s0 * kWaves + wid < ksteps; s0 += kPK) {
+            if (j0 > 0 || s0 > 0) load_w2(s0, j0);
+            u32x4 hv[kPK], lv[kPK];
+#pragma unroll
+            for (int u = 0; u < kPK; ++u) {
+                const int st = (s0 + u) * kWaves + wid;
+                const int o = aoff + (st < ksteps ? st : 0) * kStep;
+                if constexpr (kBF16) {
+                    hv[u] = *(const u32x4*)(ahi + o);
+                    lv[u] = *(const u32x4*)(alo + o);
                 } else {
-#pragma unroll
-                    for (int u = 0; u < kPF; ++u) {
-                        const int k = kb + u * 32 + kq * 8;
-                        wf[u] = (j < nb && k < m) ? *(const bf16x8*)(W2 + (int64_t)j * m + k)
-                                                  : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-                    }
-                }
-                // all of this chunk's a1 fragments are read from LDS first, so
-                // their latencies overlap; rows >= HD_RB read row 0 and are
-                // zeroed afterwards (their MFMA rows are discarded anyway)
-                bf16x8 hv[kPF], lv[kPF];
-                const int arow_off = (arow ? r16 : 0) * astride;
-#pragma unroll
-                for (int u = 0; u < kPF; ++u) {
-                    const int k = (kb + u * 32 < mpad ? kb + u * 32 : 0) + kq * 8;
-                    hv[u] = *(const bf16x8*)(ahi + arow_off + k);
-                    lv[u] = *(const bf16x8*)(alo + arow_off + k);
-                }
-                const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                for (int u = 0; u < kPF; ++u) {
-                    if (kb + u * 32 >= mpad) break;          // uniform: mpad % 32 == 0
-                    const bf16x8_t bv = __builtin_bit_cast(bf16x8_t, wf[u]);
-                    const bf16x8 h = arow ? hv[u] : zero8;
-                    const bf16x8 l = arow ? lv[u] : zero8;
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, h), bv, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, l), bv, acc, 0, 0, 0);
+                    hv[u] = *(const u32x4*)(a32 + o);
                 }
             }
-            const int col = nblk * 16 + r16;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = 4 * kq + v;
-                const float bias = nblk == wid ? b2v : (b2 && col < nb ? b2[col] : 0.0f);
-                if (row < HD_RB && col < nb) z[row * nbpad + col] = acc[v] + bias;
+            for (int u = 0; u < kPK; ++u) {
+                if ((s0 + u) * kWaves + wid >= ksteps) break;          // uniform
+                if constexpr (kBF16) {
+#pragma unroll
+                    for (int j = 0; j < kPB; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8_t, hv[u]),
+                            __builtin_bit_cast(bf16x8_t, wf[u][j]), acc[j], 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < kPB; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8_t, lv[u]),
+                            __builtin_bit_cast(bf16x8_t, wf[u][j]), acc[j], 0, 0, 0);
+                } else {
+                    // v_mfma_f32_16x16x4_f32 takes one k of each lane group
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int j = 0; j < kPB; ++j)
+                            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                __uint_as_float(hv[u][e]), __uint_as_float(wf[u][j][e]), acc[j],
+                                0, 0, 0);
+                }
             }
         }
-    } else {
-        const float* W2 = (const float*)w2;
-        for (int e = tid; e < HD_RB * nb; e += HD_THREADS) {
-            const int r = e / nb, j = e % nb;
-            // m % 4 == 0 and 16-byte aligned rows: float4 reads, the same
-            // sequential fma chain
-            const float4* wrow = (const float4*)(W2 + (int64_t)j * m);
-            const float4* arow = (const float4*)(a32 + r * m);
-            float s = 0.0f;
-            for (int u = 0; u < (m >> 2); ++u) {
-                const float4 a = arow[u], w = wrow[u];
-                s = fmaf(a.x, w.x, s);
-                s = fmaf(a.y, w.y, s);
-                s = fmaf(a.z, w.z, s);
-                s = fmaf(a.w, w.w, s);
-            }
-            z[r * nbpad + j] = s + (b2 ? b2[j] : 0.0f);
+        if (kq == 0) {
+#pragma unroll
+            for (int j = 0; j < kPB; ++j)
+                if (j0 + j < nblocks)
+#pragma unroll
+                    for (int r = 0; r < HD_RB; ++r)
+                        z[(wid * HD_RB + r) * nbpad + (j0 + j) * 16 + r16] = acc[j][r];
         }
     }
+    static_assert(HD_RB == 4 && kWaves == HD_RB, "accumulator rows, one wave per row");
     __syncthreads();
 
     // 3) softmax, expectation, EMA, integerisation: one wave per row
-    for (int r = wid; r < HD_RB; r += HD_THREADS / 64) {
-        const int gr = row0 + r;
-        if (gr >= B) continue;
-        float den = 1.0f, num = 0.0f;
-        if constexpr (kReg) {
+    if (gr >= B) return;
+    float zl[4];                                  // -inf (0 for the regression head) past nb
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = lane + 64 * i;
-                if (j < nb) num += fmaxf(z[r * nbpad + j], 0.0f) * binv[i];
-            }
-            num = wave_sum_f32(num) + b4;
-        } else {
-            float zmax = -INFINITY;
-            for (int j = lane; j < nb; j += 64) zmax = fmaxf(zmax, z[r * nbpad + j]);
-            zmax = wave_max_f32(zmax);
-            den = 0.0f;
+    for (int i = 0; i < 4; ++i) {
+        const int j = lane + 64 * i;
+        const int jc = j < nb ? j : 0;
+        float t = z[wid * nbpad + jc];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = lane + 64 * i;
-                if (j < nb) {
-                    const float e = expf(z[r * nbpad + j] - zmax);
-                    den += e;
-                    num += e * binv[i];
-                }
+        for (int w = 1; w < kWaves; ++w) t += z[(w * HD_RB + wid) * nbpad + jc];
+        t += b2v[i];
+        zl[i] = j < nb ? t : kReg ? 0.0f : -INFINITY;
+    }
+    float den = 1.0f, num = 0.0f;
+    if constexpr (kReg) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lane + 64 * i < nb) num += fmaxf(zl[i], 0.0f) * binv[i];
+        num = wave_total_f32(num) + b4;
+    } else {
+        const float zmax = wave_top_f32(fmaxf(fmaxf(zl[0], zl[1]), fmaxf(zl[2], zl[3])));
+        den = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (lane + 64 * i < nb) {
+                const float e = expf(zl[i] - zmax);
+                den += e;
+                num += e * binv[i];
             }
-            den = wave_sum_f32(den);
-            num = wave_sum_f32(num);
         }
-        if (lane == 0) {
-            const float E = kReg ? num : num / den;
-            expected[gr] = E;
-            float y = E;
-            if (ema_alpha > 0.0f) {
-                const float prev = r == wid ? ema_prev : ema_state[gr];
-                y = ema_init ? E : ema_alpha * E + (1.0f - ema_alpha) * prev;
-                ema_state[gr] = y;
-            }
-            if (rem_len) {
-                float q = rintf(y);
-                int32_t li;
-                if (!(q >= 1.0f)) li = 1;
-                else if (q >= (float)len_max) li = len_max;
-                else li = (int32_t)q;
-                rem_len[gr] = li;
-            }
+        den = wave_total_f32(den);
+        num = wave_total_f32(num);
+    }
+    if (lane == 0) {
+        const float E = kReg ? num : num / den;
+        expected[gr] = E;
+        float y = E;
+        if (ema_alpha > 0.0f) {
+            y = ema_init ? E : ema_alpha * E + (1.0f - ema_alpha) * ema_prev;
+            ema_state[gr] = y;
+        }
+        if (rem_len) {
+            float q = rintf(y);
+            int32_t li;
+            if (!(q >= 1.0f)) li = 1;
+            else if (q >= (float)len_max) li = len_max;
+            else li = (int32_t)q;
+            rem_len[gr] = li;
         }
     }
 }
@@ -1145,11 +1061,11 @@ struct FusedArgs {
     float* ema_state;
     float* expected;
     int32_t* rem_len;
-    int M, N, Kd, nb, tiles_n, ktiles, act, ema_init, len_max;
+    int M, N, Kd, nb, tiles_n, act, ema_init, len_max;
     float ema_alpha;
 };
 
-template <int NS, class SH>
+template <class SH>
 __global__ __launch_bounds__(SH::THREADS) void predict_fused_kernel(FusedArgs a) {
     constexpr int MI = SH::MI, NJ = SH::NJ, T = SH::THREADS, NW = T / 64;
     constexpr int BM = SH::BM, BN = SH::BN;
@@ -1160,14 +1076,12 @@ __global__ __launch_bounds__(SH::THREADS) void predict_fused_kernel(FusedArgs a)
     constexpr int MAXB = (NBI * (FU_NB_MAX / 32) + NW - 1) / NW;   // logit blocks per wave
     constexpr int LPR = T / BM;                  // lanes per row in the softmax
     static_assert(LPR >= 1 && (LPR & (LPR - 1)) == 0 && LPR <= 64, "lanes per row");
-    // the operand buffers of the main loop, reused for the z1 / a1 tile and
-    // then the logits
-    constexpr int kMainBytes = 2 * (SH::LDS_A + SH::LDS_B);
+    // the main loop's ring, reused for the z1 / a1 tile and then the logits
+    constexpr int kMainBytes = SH::LDS;
     constexpr int kLogitBytes = (BM * FU_NBP + 2 * FU_NB_MAX) * 4;   // logits, bin values, b2
     constexpr int kTileBytes = BM * ZST;
     constexpr int kEpiBytes = kLogitBytes > kTileBytes ? kLogitBytes : kTileBytes;
-    __shared__ __attribute__((aligned(16))) char lds_raw[kMainBytes > kEpiBytes ? kMainBytes : kEpiBytes];
-    auto lds = reinterpret_cast<char (*)[SH::LDS_A + SH::LDS_B]>(lds_raw);
+    __shared__ __attribute__((aligned(1024))) char lds_raw[kMainBytes > kEpiBytes ? kMainBytes : kEpiBytes];
     __shared__ uint32_t s_ticket;
 
     const int tid = threadIdx.x;
@@ -1176,9 +1090,10 @@ __global__ __launch_bounds__(SH::THREADS) void predict_fused_kernel(FusedArgs a)
     const int wm = wid / SH::WN, wn = wid % SH::WN;
     const int r32 = lane & 31;
     const int khalf = lane >> 5;
-    const G1Work w = g1_work(1, a.tiles_n, a.ktiles, blockIdx.x, gridDim.x);
+    const int64_t row_bytes = (int64_t)a.Kd * 2;
+    const G1Work w = g1_work<SH>(1, a.tiles_n, row_bytes, blockIdx.x, gridDim.x);
     f32x16 acc[MI][NJ];
-    g1_mainloop<2, NS, SH>(a.A, a.W, a.M, a.N, a.Kd, w, lds, acc);
+    g1_mainloop<2, SH>(a.A, a.W, a.M, a.N, row_bytes, w, lds_raw, acc);
 
     // The head's global reads (W2 fragments, b1, b2, bin values, EMA state)
     // are all requested at once: one memory latency instead of one per use.
@@ -1340,7 +1255,7 @@ __global__ __launch_bounds__(SH::THREADS) void predict_fused_kernel(FusedArgs a)
     //    them; then LPR lanes per row: + b2, softmax, mean over the bin
     //    values, EMA, integerisation
     __syncthreads();                          // every wave has read a1 from LDS
-    float* zl = (float*)&lds[0][0];
+    float* zl = (float*)lds_raw;
     float* sbin = zl + BM * FU_NBP;           // [FU_NB_MAX] bin values, then [FU_NB_MAX] b2
     if (tid < FU_NB_MAX) {
         sbin[tid] = binv;
@@ -1448,59 +1363,70 @@ __global__ __launch_bounds__(ACT_THREADS) void act_kernel(const float* __restric
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Tiles and split-K factor of one product [M, K] x [N, K]^T.  For each tile
-// shape the split is a power of two in [1, 16] that brings the workgroups
-// near one per CU (128 x 128, 128 x 64) or two per CU (64 x 64).  The shape
-// is chosen by a cost model of its two data streams: operand rows read into
-// the CUs (every A row once per column of tiles, every W row once per row of
-// tiles) at the L2's aggregate ~17 TB/s,
-// and the fp32 split-K partials written, flushed out of L2 at the end of
-// the kernel and read back at ~2.4 TB/s (both rates measured on MI355X).
+// Tiles and split-K factor of one product [M, K] x [N, K]^T: the smallest
+// cost over the 64 x 64, 128 x 64 and 128 x 128 tiles and 1 to 16 K-slices (a
+// power of two; at least two K-steps each).  The cost, in ns:
+//  * the K-steps of the busiest CU.  A step (128 bytes of every row) of the w
+//    workgroups that a CU holds at once takes at least 270, 350 or 430 ns
+//    (the ring's latency at 64 x 64, 128 x 64, 128 x 128), and its bytes at
+//    107 B/ns; in fp32, its products at 256 FLOP per cycle and 2.4 GHz.  The
+//    rings' LDS admits three, two and one workgroups;
+//  * the partials of a split product, written and read back by the next
+//    kernel, at 4.5 B/ps, and 120 ns of that kernel per plane.
+// Fitted to whole star_predict calls in captured graphs (bf16, us), which it
+// puts in the order measured:
+//   1024 x 512 x 4096: 64 x 64 with 4 slices 15.8, 128 x 64 with 4 16.9,
+//     128 x 128 with 8 17.0, 128 x 128 with 4 17.8, 64 x 64 with 2 19.3;
+//   2048 x 512 x 4096: 128 x 128 with 4 22.8, 128 x 64 with 4 23.0, 64 x 64
+//     with 2 24.0, 128 x 64 with 2 25.2, 128 x 128 with 2 26.5;
+//   512 x 512 x 4096: 64 x 64 with 8 13.3, 128 x 64 with 8 14.3, 64 x 64
+//     with 4 14.5;  64 rows: 64 x 64 with 8 11.3, with 16 12.1.
+constexpr int64_t G1_MAX_SPLIT_BYTES = STAR_NOALLOC_SCRATCH_BYTES - STAR_WS_HEADER_BYTES;
 GemmPlan plan_gemm(int M, int N, int K, int elem) {
     GemmPlan best;
     double best_cost = 0.0;
-    const int bk = G1_KBYTES / elem;
-    struct Cand { int shape, bm, bn, slots; };
-    const Cand cands[3] = {{GemmPlan::kBig, G1Big::BM, G1Big::BN, 256},
-                           {GemmPlan::kSmall, G1Small::BM, G1Small::BN, 512},
-                           {GemmPlan::kMid, G1Mid::BM, G1Mid::BN, 256}};
-    for (int ci = 0; ci < 3; ++ci) {
-        if (cands[ci].shape == GemmPlan::kMid && M > G1Mid::BM) continue;
-        GemmPlan g;
-        g.shape = cands[ci].shape;
-        const int bm = cands[ci].bm, bn = cands[ci].bn;
-        g.tiles_m = (int)ceil_div(M, bm);
-        g.tiles_n = (int)ceil_div(N, bn);
-        g.ktiles = (int)ceil_div(K, bk);
-        const int tiles = g.tiles_m * g.tiles_n;
-        int s = 1;
-        const int slots = cands[ci].slots;
-        if (tiles > 0 && tiles < 3 * slots / 4) {
-            int want = slots / tiles;
-            if (want > 16) want = 16;
-            if (want > g.ktiles / 2) want = g.ktiles / 2;
-            while (s * 2 <= want) s *= 2;
-        }
-        g.splits = s;
-        const double operands = ((double)g.tiles_n * M + (double)g.tiles_m * N) * K * elem;
-        const double partials = (double)s * M * N * 4.0;
-        const double cost = operands / 17e12 + 2.0 * partials / 2.4e12;
-        if (ci == 0 || cost < best_cost) {
-            best = g;
-            best_cost = cost;
+    struct Cand { int shape, bm, bn, at_once; double floor_ns; };
+    const Cand cands[3] = {{GemmPlan::kBig, G1Big::BM, G1Big::BN, 1, 430.0},
+                           {GemmPlan::kMid, G1Mid::BM, G1Mid::BN, 2, 350.0},
+                           {GemmPlan::kSmall, G1Small::BM, G1Small::BN, 3, 270.0}};
+    const int64_t steps = ceil_div((int64_t)K * elem, 128);
+    for (const Cand& c : cands) {
+        const int64_t tm = ceil_div(M, c.bm), tn = ceil_div(N, c.bn);
+        const double load_ns = (c.bm + c.bn) * 128 / 107.0;
+        const double mfma_ns = elem == 4 ? c.bm * c.bn * 64 / 256 / 2.4 : 0.0;
+        for (int s = 1; s <= 16; s *= 2) {
+            // a split product's partials stay within the allocation-free
+            // entry point's scratch, which one K-slice may need less of
+            const int64_t partials = (int64_t)s * M * N * 4;
+            if (s > 1 && (steps < 2 * s || partials > G1_MAX_SPLIT_BYTES)) break;
+            // nor do narrow tiles take more of it than 128 x 128 ones would,
+            // by the logit shares of the fused kernel (up to 128 bins)
+            if (s == 1 && c.shape != GemmPlan::kBig && tn > 1 &&
+                tm * c.bm * tn * FU_NB_MAX * 4 > G1_MAX_SPLIT_BYTES)
+                continue;
+            const int64_t w = ceil_div(tm * tn * s, 256);          // on the busiest CU
+            const double held = (double)(w < c.at_once ? w : c.at_once);
+            double step_ns = held * (load_ns > mfma_ns ? load_ns : mfma_ns);
+            if (step_ns < c.floor_ns) step_ns = c.floor_ns;
+            const double cost = (double)ceil_div(steps, s) * step_ns * (w / held) +
+                                (s > 1 ? partials / 4.5e3 + 120.0 * s : 0.0);
+            if ((c.shape == GemmPlan::kBig && s == 1) || cost < best_cost) {
+                best.shape = c.shape;
+                best.tiles_m = (int)tm;
+                best.tiles_n = (int)tn;
+                best.splits = s;
+                best_cost = cost;
+            }
         }
     }
     if (best.shape == GemmPlan::kBig && best.splits == 1) {
         const int hm = (int)ceil_div(M, G1Huge::BM), hn = (int)ceil_div(N, G1Huge::BN);
-        if (hm * hn >= G1_HUGE_MIN_TILES) {       // 256 x 256 tiles, 64 x 128 per wave
+        if ((int64_t)hm * hn >= G1_HUGE_MIN_TILES) {       // 256 x 256 tiles
             best.shape = GemmPlan::kHuge;
             best.tiles_m = hm;
             best.tiles_n = hn;
-            return best;
         }
     }
-    if (best.shape == GemmPlan::kBig && best.tiles_m * best.tiles_n >= G1_WIDE_MIN_TILES)
-        best.shape = GemmPlan::kWide;             // same tiles and splits, 64 x 64 per wave
     return best;
 }
 
@@ -1526,7 +1452,6 @@ PredictPlan plan_predict(const star_predict_params& p, bool tiled_ok, bool fused
     pl.gemm = g;
     pl.tiles_m = g.tiles_m;
     pl.tiles_n = g.tiles_n;
-    pl.ktiles = g.ktiles;
     const int s = g.splits;
     pl.splits = s;
     if (fused_ok && p.dtype == STAR_BF16 && fused_fits(g, p.n_bins)) {
@@ -1540,25 +1465,18 @@ PredictPlan plan_predict(const star_predict_params& p, bool tiled_ok, bool fused
         return pl;
     }
     pl.partial_bytes = (size_t)s * (size_t)p.n_req * (size_t)p.d_hidden * sizeof(float);
-    const int mpad = (p.d_hidden + 31) & ~31;
-    const int nbpad = (p.n_bins + 15) & ~15;
     pl.head_tiled = tiled_ok && p.dtype == STAR_BF16 && p.n_req >= HT_MIN_REQ &&
                     s <= HT_MAX_SPLITS;
     pl.head_rows = pl.head_tiled ? HT_ROWS : HD_RB;
-    const size_t rb = (size_t)pl.head_rows;
-    if (pl.head_tiled)
-        pl.head_lds = head_tiled_lds(p.n_bins, p.d_hidden);
-    else if (p.dtype == STAR_BF16)
-        pl.head_lds = 2 * rb * (mpad + 8) * 2 + rb * nbpad * 4;
-    else
-        pl.head_lds = rb * p.d_hidden * 4 + rb * nbpad * 4;
+    pl.head_lds = pl.head_tiled ? head_tiled_lds(p.n_bins, p.d_hidden)
+                                : head_rows_lds(p.dtype == STAR_BF16, p.d_hidden, p.n_bins);
     return pl;
 }
 
-template <int NS, class SH>
+template <class SH>
 static hipError_t launch_fused_shape(const PredictPlan& pl, const FusedArgs& a, hipStream_t stream) {
     const dim3 grid(pl.gemm.tiles_m * pl.gemm.tiles_n);
-    hipLaunchKernelGGL((predict_fused_kernel<NS, SH>), grid, dim3(SH::THREADS), 0, stream, a);
+    hipLaunchKernelGGL((predict_fused_kernel<SH>), grid, dim3(SH::THREADS), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -1584,15 +1502,14 @@ static hipError_t launch_fused(const star_predict_params& p, const PredictPlan& 
     a.Kd = p.d_model;
     a.nb = p.n_bins;
     a.tiles_n = pl.gemm.tiles_n;
-    a.ktiles = pl.gemm.ktiles;
     a.act = p.act;
     a.ema_init = p.ema_init;
     a.len_max = p.len_max;
     a.ema_alpha = p.ema_alpha;
     switch (pl.gemm.shape) {
-        case GemmPlan::kSmall: return launch_fused_shape<G1_STAGES_SMALL, G1Small>(pl, a, stream);
-        case GemmPlan::kBig: return launch_fused_shape<G1_STAGES_BIG, G1Big>(pl, a, stream);
-        case GemmPlan::kMid: return launch_fused_shape<G1_STAGES_MID, G1Mid>(pl, a, stream);
+        case GemmPlan::kSmall: return launch_fused_shape<G1Small>(pl, a, stream);
+        case GemmPlan::kBig: return launch_fused_shape<G1Big>(pl, a, stream);
+        case GemmPlan::kMid: return launch_fused_shape<G1Mid>(pl, a, stream);
     }
     return hipErrorInvalidValue;
 }
@@ -1718,7 +1635,7 @@ struct OverlapArgs {
     const char* A;
     const char* W1;
     float* Pn;
-    int M, N, Kd, splits, tiles_n, ktiles, gemm_blocks;
+    int M, N, Kd, splits, tiles_n, gemm_blocks;
     // the previous batch's head
     const float* Pp;
     const float* b1;
@@ -1731,7 +1648,6 @@ struct OverlapArgs {
     int B, m, nb, act, ema_init, len_max;
     float ema_alpha;
 };
-constexpr size_t OV_LDS = 2 * (size_t)(G1Small::LDS_A + G1Small::LDS_B);
 // W2 fragments the head role prefetches: 4 keeps the kernel at 90 VGPRs, so
 // head workgroups fit beside the product's two per CU from the start
 // (measured at 1024 x 4096 -> 512 -> 64 bins, per batch: 12.9-13.6 us with
@@ -1740,19 +1656,33 @@ constexpr size_t OV_LDS = 2 * (size_t)(G1Small::LDS_A + G1Small::LDS_B);
 // for star_predict).
 constexpr int OV_W2PF = 4;
 
-template <int kS>
+template <int kS, class SH>
 __global__ __launch_bounds__(HD_THREADS) void predict_overlap_kernel(OverlapArgs a) {
-    static_assert(G1Small::THREADS == HD_THREADS, "one block size for both roles");
-    __shared__ __attribute__((aligned(16))) char lds[2][G1Small::LDS_A + G1Small::LDS_B];
+    static_assert(SH::THREADS == HD_THREADS, "one block size for both roles");
+    __shared__ __attribute__((aligned(1024))) char lds[SH::LDS];
     if ((int)blockIdx.x < a.gemm_blocks)
-        gemm1_tile<2, G1_STAGES_SMALL, G1Small>(a.A, a.W1, a.Pn, a.M, a.N, a.Kd, a.splits,
-                                                a.tiles_n, a.ktiles, blockIdx.x, a.gemm_blocks,
-                                                lds);
+        gemm1_tile<2, SH>(a.A, a.W1, a.Pn, a.M, a.N, a.Kd, a.splits, a.tiles_n, blockIdx.x,
+                          a.gemm_blocks, lds);
     else
         head_rows<true, kS, false, OV_W2PF>(a.Pp, a.B, a.m, a.nb, a.b1, a.w2, a.b2, a.bins,
                                             a.act, a.ema_alpha, a.ema_init, a.ema_state,
                                             a.expected, a.rem_len, a.len_max, 0.0f,
-                                            (int)blockIdx.x - a.gemm_blocks, &lds[0][0]);
+                                            (int)blockIdx.x - a.gemm_blocks, lds);
+}
+
+template <class SH>
+static hipError_t launch_overlap_shape(int head_blocks, const OverlapArgs& a,
+                                       hipStream_t stream) {
+    const dim3 g((unsigned)(a.gemm_blocks + head_blocks)), t(HD_THREADS);
+    switch (a.splits) {
+        case 1: hipLaunchKernelGGL((predict_overlap_kernel<1, SH>), g, t, 0, stream, a); break;
+        case 2: hipLaunchKernelGGL((predict_overlap_kernel<2, SH>), g, t, 0, stream, a); break;
+        case 4: hipLaunchKernelGGL((predict_overlap_kernel<4, SH>), g, t, 0, stream, a); break;
+        case 8: hipLaunchKernelGGL((predict_overlap_kernel<8, SH>), g, t, 0, stream, a); break;
+        case 16: hipLaunchKernelGGL((predict_overlap_kernel<16, SH>), g, t, 0, stream, a); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPlan& pl,
@@ -1764,10 +1694,21 @@ hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPla
     if (pl.fused) return hipErrorInvalidValue;
     if (p.n_req == 0 || (!hidden_next && !partials_prev)) return hipSuccess;
     const bool bf16 = p.dtype == STAR_BF16;
-    const GemmPlan& g = pl.gemm;
     const int head_blocks = (int)ceil_div(p.n_req, HD_RB);
-    const bool one = hidden_next && partials_prev && bf16 && g.shape == GemmPlan::kSmall &&
-                     !pl.head_tiled && pl.head_rows == HD_RB && pl.head_lds <= OV_LDS &&
+    // Beside the head's workgroups, 64 x 64 tiles that need two workgroups
+    // per CU do worse than half as many 128 x 64 ones (97.0 against 94.6 us
+    // for 8 batches of 1024 x 512 x 4096).  The sums, over the same K-slices
+    // in the same order, are the same.
+    GemmPlan g = pl.gemm;
+    if (bf16 && g.shape == GemmPlan::kSmall && g.tiles_m * g.tiles_n * g.splits > 256) {
+        g.shape = GemmPlan::kMid;
+        g.tiles_m = (int)ceil_div(p.n_req, G1Mid::BM);
+    }
+    const bool mid = g.shape == GemmPlan::kMid;
+    const size_t lds = mid ? G1Mid::LDS : G1Small::LDS;
+    const bool one = hidden_next && partials_prev && bf16 &&
+                     (mid || g.shape == GemmPlan::kSmall) && !pl.head_tiled &&
+                     pl.head_rows == HD_RB && pl.head_lds <= lds &&
                      head_blocks <= HD_LOWREG_GROUPS;
     if (!one) {          // the two kernels one after the other, same results
         if (partials_prev) {
@@ -1792,7 +1733,6 @@ hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPla
     a.Kd = p.d_model;
     a.splits = g.splits;
     a.tiles_n = g.tiles_n;
-    a.ktiles = g.ktiles;
     a.gemm_blocks = g.tiles_m * g.tiles_n * g.splits;
     a.Pp = partials_prev;
     a.b1 = b1;
@@ -1809,16 +1749,8 @@ hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPla
     a.ema_init = p.ema_init;
     a.len_max = p.len_max;
     a.ema_alpha = p.ema_alpha;
-    const dim3 grid((unsigned)(a.gemm_blocks + head_blocks));
-    switch (g.splits) {
-        case 1: hipLaunchKernelGGL(predict_overlap_kernel<1>, grid, dim3(HD_THREADS), 0, stream, a); break;
-        case 2: hipLaunchKernelGGL(predict_overlap_kernel<2>, grid, dim3(HD_THREADS), 0, stream, a); break;
-        case 4: hipLaunchKernelGGL(predict_overlap_kernel<4>, grid, dim3(HD_THREADS), 0, stream, a); break;
-        case 8: hipLaunchKernelGGL(predict_overlap_kernel<8>, grid, dim3(HD_THREADS), 0, stream, a); break;
-        case 16: hipLaunchKernelGGL(predict_overlap_kernel<16>, grid, dim3(HD_THREADS), 0, stream, a); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return mid ? launch_overlap_shape<G1Mid>(head_blocks, a, stream)
+               : launch_overlap_shape<G1Small>(head_blocks, a, stream);
 }
 
 // ---------------------------------------------------------------------------

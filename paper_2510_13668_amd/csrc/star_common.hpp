@@ -79,6 +79,35 @@ __device__ inline int dpp_i32(int v, int ident) {
     return __builtin_amdgcn_update_dpp(ident, v, kCtrl, kRowMask, 0xF, false);
 }
 
+// Sum and maximum over the 64 lanes by DPP, in every lane (for the sum, lanes
+// without a source add 0; NaN is passed over by the maximum, as by fmaxf).
+template <int kCtrl, int kRowMask>
+__device__ inline float dpp_f32(float v, float ident) {
+    return __int_as_float(
+        dpp_i32<kCtrl, kRowMask>(__float_as_int(v), __float_as_int(ident)));
+}
+__device__ inline float readlane_f32(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ inline float wave_total_f32(float v) {
+    v += dpp_f32<kDppRowShr1, 0xF>(v, 0.0f);
+    v += dpp_f32<kDppRowShr2, 0xF>(v, 0.0f);
+    v += dpp_f32<kDppRowShr4, 0xF>(v, 0.0f);
+    v += dpp_f32<kDppRowShr8, 0xF>(v, 0.0f);
+    v += dpp_f32<kDppRowBcast15, 0xA>(v, 0.0f);
+    v += dpp_f32<kDppRowBcast31, 0xC>(v, 0.0f);
+    return readlane_f32(v, kWave - 1);
+}
+__device__ inline float wave_top_f32(float v) {
+    v = fmaxf(v, dpp_f32<kDppRowShr1, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_f32<kDppRowShr2, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_f32<kDppRowShr4, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_f32<kDppRowShr8, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_f32<kDppRowBcast15, 0xA>(v, -INFINITY));
+    v = fmaxf(v, dpp_f32<kDppRowBcast31, 0xC>(v, -INFINITY));
+    return readlane_f32(v, kWave - 1);
+}
+
 // Inclusive prefix sum over the 64 lanes (lane order).
 __device__ inline int wave_incl_add_i32(int v) {
     v += dpp_i32<kDppRowShr1, 0xF>(v, 0);

@@ -10,16 +10,16 @@
 namespace star {
 
 struct GemmPlan {
-    int tiles_m = 0, tiles_n = 0, ktiles = 0, splits = 1;
-    enum { kSmall = 0, kBig = 1, kWide = 2, kHuge = 3, kMid = 4 };
-    int shape = kBig;     // 64 x 64 tiles on 4 waves; 128 x 128 on 8; 128 x 128 on 4;
-                          // 256 x 256 on 8; 128 x 64 on 8
+    int tiles_m = 0, tiles_n = 0, splits = 1;
+    enum { kSmall = 0, kBig = 1, kHuge = 2, kMid = 3 };
+    int shape = kBig;     // 64 x 64 tiles on 4 waves; 128 x 128 on 8; 256 x 256 on 8;
+                          // 128 x 64 on 4
 };
 GemmPlan plan_gemm(int M, int N, int K, int elem);
 
 struct PredictPlan {
     GemmPlan gemm;
-    int tiles_m = 0, tiles_n = 0, ktiles = 0, splits = 1;
+    int tiles_m = 0, tiles_n = 0, splits = 1;
     size_t partial_bytes = 0;   // fp32 split-K partials [splits, B, m]
     size_t head_lds = 0;        // dynamic LDS of the head kernel
     int head_rows = 4;          // rows per head workgroup

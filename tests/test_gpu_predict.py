@@ -148,6 +148,44 @@ def test_random_single_row_tile_products():
                   len_max=32768)
 
 
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("B,m", [(1, 64), (64, 72), (65, 64), (129, 136), (700, 504)])
+@pytest.mark.parametrize("kb", [16, 48, 64, 112, 128, 144, 384, 400, 1168])
+def test_ring_edges(dtype, B, m, kb):
+    """The product's ring at its edges: rows of kb bytes of K below one step,
+    whole steps, partial last steps (every split of them included), fewer
+    steps than slots, and rows and columns around the tiles' edges; with bin
+    counts around the head's blocks of 16."""
+    d = kb // (2 if dtype == synth.BF16 else 4)
+    nb = 1 + (B * 7 + kb) % 67
+    rng = np.random.default_rng(B + m + kb)
+    h = rng.standard_normal((B, d)).astype(np.float32)
+    w1 = (rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32)
+    w2 = (rng.standard_normal((nb, m)) / np.sqrt(m)).astype(np.float32)
+    b2 = (rng.standard_normal(nb) * 0.1).astype(np.float32)
+    if dtype == synth.BF16:
+        h, w1, w2 = (synth.f32_to_bf16_bits(a) for a in (h, w1, w2))
+    print(f"ring dtype={dtype} B={B} d={d} m={m} nb={nb}", flush=True)
+    _run_case(h, w1, w2, synth.bin_values(nb, 1.0, 32768.0), dtype=dtype, act=synth.ACT_GELU,
+              b2=b2, len_max=32768)
+
+
+@pytest.mark.parametrize("d", [8, 40, 136, 168, 328])
+def test_ring_edges_256_tiles(d):
+    """The same for the 256 x 256 tile, whose wave groups alternate: below,
+    at and past the ring's five half-line slots, ragged rows and columns."""
+    B, m, nb = 16450, 1000, 20
+    rng = np.random.default_rng(d)
+    h = synth.f32_to_bf16_bits(rng.standard_normal((B, d)).astype(np.float32))
+    w1 = synth.f32_to_bf16_bits((rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32))
+    w2 = synth.f32_to_bf16_bits((rng.standard_normal((nb, m)) / np.sqrt(m)).astype(np.float32))
+    sample = np.unique(np.concatenate([np.arange(130), np.arange(B - 130, B),
+                                       rng.choice(B, 200, replace=False)]))
+    print(f"ring 256 tiles d={d}", flush=True)
+    _run_case(h, w1, w2, synth.bin_values(nb, 1.0, 32768.0), dtype=synth.BF16,
+              act=synth.ACT_RELU, len_max=32768, sample=sample)
+
+
 def _splits(B, d, m, nb):
     """Split-K planes the plan takes, from the workspace size (host only)."""
     from paper_2510_13668_amd import star
