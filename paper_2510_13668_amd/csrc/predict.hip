@@ -1697,13 +1697,23 @@ hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPla
     const int head_blocks = (int)ceil_div(p.n_req, HD_RB);
     // Beside the head's workgroups, 64 x 64 tiles that need two workgroups
     // per CU do worse than half as many 128 x 64 ones (97.0 against 94.6 us
-    // for 8 batches of 1024 x 512 x 4096).  The sums, over the same K-slices
-    // in the same order, are the same.
+    // for 8 batches of 1024 x 512 x 4096).  128 x 128 tiles, whose workgroups
+    // are not the head's size, give way to them where the product is short
+    // and both roles fit the chip in two passes (8 batches, two launches
+    // against one: 177 and 143 us at 705 x 440 x 7200, 189 and 176 at 1500 x
+    // 904 x 2000; but 198 and 206 at 2048 x 512 x 4096, 472 and 551 at 1789
+    // x 928 x 7416, where the narrow tiles load half as much again).  The
+    // sums, over the same K-slices in the same order, are the same.
     GemmPlan g = pl.gemm;
-    if (bf16 && g.shape == GemmPlan::kSmall && g.tiles_m * g.tiles_n * g.splits > 256) {
-        g.shape = GemmPlan::kMid;
-        g.tiles_m = (int)ceil_div(p.n_req, G1Mid::BM);
-    }
+    GemmPlan m = g;
+    m.shape = GemmPlan::kMid;
+    m.tiles_m = (int)ceil_div(p.n_req, G1Mid::BM);
+    m.tiles_n = (int)ceil_div(p.d_hidden, G1Mid::BN);
+    const int64_t steps = ceil_div((int64_t)p.d_model * 2, (int64_t)G1Mid::STEP * g.splits);
+    if (bf16 && ((g.shape == GemmPlan::kSmall && g.tiles_m * g.tiles_n * g.splits > 256) ||
+                 (g.shape == GemmPlan::kBig && steps <= 16 &&
+                  (int64_t)m.tiles_m * m.tiles_n * m.splits + head_blocks <= 3 * 256)))
+        g = m;
     const bool mid = g.shape == GemmPlan::kMid;
     const size_t lds = mid ? G1Mid::LDS : G1Small::LDS;
     const bool one = hidden_next && partials_prev && bf16 &&
