@@ -285,9 +285,9 @@ star_status star_score_migrations(const star_score_params* p, const int32_t* cur
  * Rounds whose curves fit on-chip (and with at most 8192 requests) skip
  * the projection kernel: every scoring workgroup builds the curves itself
  * and one of them writes `load`; other sizes run the projection first, and
- * where it takes request slices (see star_project_load_workspace_size) and
- * the curves do not fit on-chip, it also writes the scoring's bucket-major
- * curve terms, so no separate preparation pass runs.
+ * where n_buckets <= 1024, the request arrays are 16-byte aligned and the
+ * curves do not fit on-chip, it also writes the scoring's curve terms, so no
+ * separate preparation pass runs.
  * ---------------------------------------------------------------------- */
 size_t star_project_and_score_workspace_size(const star_score_params* p);
 

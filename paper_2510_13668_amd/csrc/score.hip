@@ -1860,16 +1860,12 @@ __device__ __forceinline__ int best_sorted(const TopkArgs& a, SelShared<TK_THREA
         for (int u = 0; u < 8; ++u) sel |= (code(j, u) <= cstar ? 1u : 0u) << (j * 8 + u);
     int tot;
     int pos = block_excl_i32<TK_THREADS>(__builtin_popcount(sel), sh, &tot);
-    if (sel) {                                            // few threads have any
-#pragma unroll
-        for (int j = 0; j < TK_CODE_V; ++j)
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (sel & (1u << (j * 8 + u))) {
-                    sl.ci[pos] = (uint32_t)((j * TK_THREADS + tid) * 8 + u);
-                    sl.cc[pos] = code(j, u);
-                    ++pos;
-                }
+    // few threads have any: one turn per set bit, and the code is read again
+    // with the key (with a branch per code, to place the code as well, the
+    // whole kernel took 16.6 us at 32768 x 64 candidates against 15.6)
+    for (; sel; sel &= sel - 1) {
+        const int bit = __ffs((int)sel) - 1;
+        sl.ci[pos++] = (uint32_t)(((bit >> 3) * TK_THREADS + tid) * 8 + (bit & 7));
     }
     __syncthreads();
     int64_t s = 0;
@@ -1877,7 +1873,7 @@ __device__ __forceinline__ int best_sorted(const TopkArgs& a, SelShared<TK_THREA
     uint16_t c = 0;
     if (tid < nle) {
         r = sl.ci[tid];
-        c = sl.cc[tid];
+        c = a.bcode[r];
         s = a.best_score[r];
     }
     const int nr = a.top_k < nle ? a.top_k : nle;

@@ -43,6 +43,37 @@ def test_workload_true_lengths(name, fused):
            fused=fused)
 
 
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "misaligned"])
+@pytest.mark.parametrize("N,n,b,K,top_k", [
+    (1, 3, 4, 1024, 2),         # one request: no whole group of four; every thread a bucket
+    (6, 60, 1, 50, 16),         # more instances than requests
+    (4099, 9, 16, 400, 256),    # two groups per thread, a ragged last one
+    (8191, 3, 3, 1023, 0),      # longest stream of one workgroup per instance
+    (300, 4, 2, 1025, 16),      # one bucket too many: the chunked projection
+])
+def test_projection_with_planes(N, n, b, K, top_k, offset):
+    """Curves and curve planes from one launch (K <= 1024, 16-byte aligned
+    arrays, fewer requests than the sliced projection takes) against the two
+    launches of other sizes and alignments, with invalid requests."""
+    rng = np.random.default_rng(N + K + offset)
+    cur, rem, inst = synth.random_requests(rng, N, n, cur_hi=5000, len_hi=b * K + 50)
+    if N > 4:
+        inst[2], cur[3], rem[N - 1] = n, 0, -1
+    print(f"planes N={N} n={n} b={b} K={K} top_k={top_k} offset={offset}", flush=True)
+    rs = Rescheduler(N, n, b, K, top_k, True, True)
+
+    def dev(a):
+        t = torch.empty(N + 8, dtype=torch.int32, device="cuda")[offset:offset + N]
+        t.copy_(torch.from_numpy(a))
+        return t
+
+    rs.run(dev(cur), dev(rem), dev(inst))
+    gpu = rs.result()
+    ref = oracle.round_(cur, rem, inst, n_inst=n, bucket=b, n_buckets=K, top_k=top_k)
+    assert_round_equal(gpu, ref)
+    assert rs.ws_score.read_device_error() == ref["flags"]
+
+
 def test_long_output_stress_mix():
     rng = np.random.default_rng(5)
     N, n = 4096, 16
