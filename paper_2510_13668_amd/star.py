@@ -157,6 +157,11 @@ def _ptrs(*ts):
     return out
 
 
+def _ptr(t: Optional[torch.Tensor]):
+    """The address of one tensor (see _ptrs)."""
+    return _ptrs(t)[0]
+
+
 def _stream(stream) -> int:
     """The hipStream_t of `stream`, or of the current device's current stream."""
     if stream is not None:
@@ -231,7 +236,7 @@ def predict_overlap(p: PredictParams, hidden_next, ws_next, ws_prev, w1, b1, w2,
     (None: no product), in one launch where the plan allows."""
     nbytes = (ws_next or ws_prev).nbytes
     _check("star_predict_overlap", lib().star_predict_overlap(
-        ctypes.byref(p), *_ptrs(hidden_next), ws_next.ptr if ws_next else None,
+        ctypes.byref(p), _ptr(hidden_next), ws_next.ptr if ws_next else None,
         ws_prev.ptr if ws_prev else None,
         *_ptrs(w1, b1, w2, b2, bin_values, ema_state, expected_len, rem_len), nbytes,
         _stream(stream)))
