@@ -12,12 +12,15 @@
 // its requests with k_e > k (suffix sums of histograms indexed by k_e), and
 // D_P the partial-bucket histogram.
 //
-// Long request streams (16-byte aligned arrays, K <= 1024): one workgroup
-// per (instance, slice of the requests) scatters its instance's requests of
-// its slice into LDS histograms by k_e and stores them; the last workgroup
-// of an instance to finish sums the slices' histograms, runs the suffix scan
-// and writes load[i, :].  So each request is read once per instance by a
-// few hundred workgroups at once, instead of the whole stream by each of n.
+// Request streams of 8192 to 32768 (16-byte aligned arrays, K <= 1024): one
+// workgroup per instance reads every request's instance, packs the places of
+// its own requests and scatters those into LDS histograms by k_e, runs the
+// suffix scan and writes load[i, :].
+//
+// Longer streams, or many requests per instance: one workgroup per (instance,
+// slice of the requests) scatters its instance's requests of its slice into
+// LDS histograms by k_e and stores them; the last workgroup of an instance to
+// finish sums the slices' histograms and goes on as above.
 //
 // Shorter streams whose curve planes the scoring wants (K <= 1024) take the
 // same kernel with one slice.
@@ -190,6 +193,20 @@ constexpr int PS_RV = 2;               // 16-byte reads per thread and array in 
 // instances it took 11.4 us against 4.6 + 4 us for the chunked kernel and
 // the separate plane preparation: the meeting's latency dominates)
 constexpr int PS_MIN_REQ = 8192;
+constexpr int PW_RV = 8;               // 16-byte reads of instances per thread and round
+constexpr int PW_U = 2;                // list entries per thread in flight
+static_assert(PS_THREADS * PW_RV * 4 <= 65536 && PW_RV <= 8, "16-bit places, 32 marks");
+// One workgroup per instance instead of slices that meet (us per call, K = 1024; split
+// kernel, this one; blocks: an instance's requests are neighbours; crowded: a
+// quarter of all requests on one instance besides):
+//   32768 x 64: blocks 10.1, 6.1, shuffled 11.1, 6.9, crowded 10.4, 9.4
+//   32768 x 16: blocks 9.5, 6.8, shuffled 10.3, 7.6, crowded 9.5, 10.3
+//   16384 x 8:  blocks 8.4, 6.4, shuffled 8.8, 7.1, crowded 8.3, 8.1
+//   8192 x 3:   blocks 8.3, 6.8, shuffled 8.4, 7.2, crowded 8.3, 7.6
+//   32768 x 8:  blocks 9.1, 8.0, shuffled 9.3, 9.2, crowded 8.9, 11.6
+//   65536 x 64: blocks 11.1, 8.2, shuffled 13.5, 10.1, crowded 13.2, 15.9
+constexpr int PW_MAX_REQ = 32768;      // one round of the stream
+constexpr int PW_MAX_PER_INST = 2048;  // requests per instance, on average
 
 struct SplitArgs {
     const int32_t* cur;
@@ -203,11 +220,71 @@ struct SplitArgs {
     int N, n, b, K, KP, slices, slice_len;
 };
 
+// one request into the histograms by k_e
+__device__ __forceinline__ void scatter_request(int cr, int lr, int b, int64_t H, int64_t alpha0,
+                                                int64_t* hA, int64_t* hN, int64_t* hP) {
+    // l' < 2^31, 1 <= b < 2^31: 32-bit division is exact
+    const uint32_t lp = (uint32_t)((int64_t)lr < H ? (int64_t)lr : H);
+    const uint32_t ke = lp / (uint32_t)b;
+    const int64_t mu = (int64_t)(lp - ke * (uint32_t)b);
+    if (ke > 0) {
+        atomicAdd((unsigned long long*)&hA[ke], (unsigned long long)((int64_t)b * cr + alpha0));
+        atomicAdd((unsigned long long*)&hN[ke], 1ull);
+    }
+    if (mu > 0) {                                     // then k_e < K
+        const int64_t pr = mu * cr + mu * (int64_t)ke * b + mu * (mu - 1) / 2;
+        atomicAdd((unsigned long long*)&hP[ke], (unsigned long long)pr);
+    }
+}
+
+// The curve of instance i, and its scoring planes where they are wanted, from
+// the histograms' sums: thread t holds bucket q = K-1-t, with xa and xn the sums
+// of h_A and h_N at q+1 and xp that of h_P at q (zeros past K).  hA and hN are
+// overwritten after the first scan's barriers.
+__device__ __forceinline__ void finish_curve(const SplitArgs& a, int64_t xa, int64_t xn, int64_t xp,
+                                             int64_t* hA, int64_t* hN, int64_t* tmp) {
+    const int tid = threadIdx.x, i = blockIdx.x, K = a.K, b = a.b;
+    const int q = K - 1 - tid;
+    const bool live = tid < K;
+    // inclusive prefix in thread order = suffix sums over k_e > q
+    block_incl_add2_i64<PS_THREADS>(xa, xn, tmp);
+    const int64_t bb = (int64_t)b * b;
+    const int64_t Lq = xa + bb * q * xn + xp;
+    if (live) a.load[(int64_t)i * K + q] = Lq;
+    if (!a.planes.tpm) return;
+
+    // The scoring's planes of this instance (see CurvePlanes):
+    // SM (suffix max of L) is the inclusive prefix max in this thread order;
+    // PM (max of L[j] + b^2 j over j < k) takes the forward order j = t,
+    // with L passed through LDS.
+    const CurvePlanes& pl = a.planes;
+    if (live) hA[q] = Lq;
+    __syncthreads();
+    const int j = tid;
+    int64_t sm = live ? Lq : INT64_MIN;
+    int64_t pm = j < K ? hA[j] + bb * j : INT64_MIN;
+    block_incl_max2_i64<PS_THREADS>(sm, pm, tmp);
+    hN[j] = pm;                                   // inclusive; PM[j] is thread j-1's
+    __syncthreads();
+    if (live) {
+        pl.tl[q * pl.sk + i * pl.st] = Lq;
+        if (q > 0) pl.tsm[(q - 1) * pl.sk + i * pl.st] = sm;
+        else pl.peak[i] = sm;
+    }
+    if (j < K) pl.tpm[j * pl.sk + i * pl.st] = j > 0 ? hN[j - 1] : INT64_MIN;
+    if (tid == 0) {
+        pl.tpm[K * pl.sk + i * pl.st] = hN[K - 1];
+        pl.tl[K * pl.sk + i * pl.st] = INT64_MIN;
+        pl.tsm[(K - 1) * pl.sk + i * pl.st] = INT64_MIN;
+        pl.tsm[K * pl.sk + i * pl.st] = INT64_MIN;
+    }
+}
+
 // kMeet: the slices of an instance meet at a counter.  Otherwise one workgroup
 // takes an instance's whole stream and its histograms never leave LDS: for
-// shorter streams whose curve planes are wanted too.  One launch then does
-// what project_load_kernel and score_prep_kernel do in two: whole calls at 4096
-// requests x 16 instances x 512 buckets 26.1 -> 24.0 us, 7000 x 40 x 200
+// streams below the split's whose curve planes are wanted too.  One launch then
+// does what project_load_kernel and score_prep_kernel do in two: whole calls at
+// 4096 requests x 16 instances x 512 buckets 26.1 -> 24.0 us, 7000 x 40 x 200
 // without a top-k 17.1 -> 12.7, 100 x 20 x 300 21.3 -> 19.3.
 template <bool kMeet>
 __global__ __launch_bounds__(PS_THREADS) void project_split_kernel(SplitArgs a) {
@@ -233,18 +310,7 @@ __global__ __launch_bounds__(PS_THREADS) void project_split_kernel(SplitArgs a) 
         if (lr < 1) f |= STAR_DEV_BAD_REM;
         bad |= f;
         if (f || s != i) return;
-        // l' < 2^31, 1 <= b < 2^31: 32-bit division is exact
-        const uint32_t lp = (uint32_t)((int64_t)lr < H ? (int64_t)lr : H);
-        const uint32_t ke = lp / (uint32_t)b;
-        const int64_t mu = (int64_t)(lp - ke * (uint32_t)b);
-        if (ke > 0) {
-            atomicAdd((unsigned long long*)&hA[ke], (unsigned long long)((int64_t)b * cr + alpha0));
-            atomicAdd((unsigned long long*)&hN[ke], 1ull);
-        }
-        if (mu > 0) {                                 // then k_e < K
-            const int64_t pr = mu * cr + mu * (int64_t)ke * b + mu * (mu - 1) / 2;
-            atomicAdd((unsigned long long*)&hP[ke], (unsigned long long)pr);
-        }
+        scatter_request(cr, lr, b, H, alpha0, hA, hN, hP);
     };
     const int4* s4 = (const int4*)a.inst;
     const int4* c4 = (const int4*)a.cur;
@@ -327,38 +393,131 @@ __global__ __launch_bounds__(PS_THREADS) void project_split_kernel(SplitArgs a) 
         xn = hN[q + 1];
         xp = hP[q];
     }
-    // inclusive prefix in thread order = suffix sums over k_e > q
-    block_incl_add2_i64<PS_THREADS>(xa, xn, tmp);
-    const int64_t bb = (int64_t)b * b;
-    const int64_t Lq = xa + bb * q * xn + xp;
-    if (live) a.load[(int64_t)i * K + q] = Lq;
-    if (!a.planes.tpm) return;
+    finish_curve(a, xa, xn, xp, hA, hN, tmp);
+}
 
-    // The scoring's planes of this instance (see CurvePlanes):
-    // SM (suffix max of L) is the inclusive prefix max in this thread order;
-    // PM (max of L[j] + b^2 j over j < k) takes the forward order j = t,
-    // with L passed through LDS.
-    const CurvePlanes& pl = a.planes;
-    if (live) hA[q] = Lq;
-    __syncthreads();
-    const int j = tid;
-    int64_t sm = live ? Lq : INT64_MIN;
-    int64_t pm = j < K ? hA[j] + bb * j : INT64_MIN;
-    block_incl_max2_i64<PS_THREADS>(sm, pm, tmp);
-    hN[j] = pm;                                   // inclusive; PM[j] is thread j-1's
-    __syncthreads();
-    if (live) {
-        pl.tl[q * pl.sk + i * pl.st] = Lq;
-        if (q > 0) pl.tsm[(q - 1) * pl.sk + i * pl.st] = sm;
-        else pl.peak[i] = sm;
+// One workgroup per instance takes the whole stream, so nothing has to meet.  It reads every request's instance, but
+// lengths only of its own requests: each thread marks those among its 32, a
+// prefix sum over the wave packs their places into a list, and the threads
+// then take one list entry each, so that every lane has a request whatever
+// their order in the stream.  The validity of all requests is checked in
+// shares of N / n per workgroup.  A chain of latencies bounds it: 6.1 us at
+// 32768 x 64, K = 1024, of which a launch on its own is about 2.5, where
+// slices that meet took 10.1.  Below 8192 requests it is 0.8-1.9 us slower than
+// one slice of the split kernel (100 to 8191 requests, 3 to 64 instances).
+__global__ __launch_bounds__(PS_THREADS) void project_whole_kernel(SplitArgs a) {
+    __shared__ int64_t hA[PS_MAX_K + 2];   // alpha_r by k_e (1..K)
+    __shared__ int64_t hN[PS_MAX_K + 2];   // request count by k_e (1..K)
+    __shared__ int64_t hP[PS_MAX_K + 2];   // partial-bucket contributions by k_e (0..K-1)
+    __shared__ int64_t tmp[2 * PS_THREADS / 64];
+    __shared__ uint16_t list[PS_THREADS * PW_RV * 4];   // this instance's requests of a round
+    __shared__ int count;
+    const int tid = threadIdx.x, i = blockIdx.x;
+    const int K = a.K, b = a.b, KP = a.KP, n = a.n;
+    const int64_t H = (int64_t)b * K;
+    const int64_t alpha0 = (int64_t)b * (b - 1) / 2;
+    const int q1 = a.N >> 2;                        // whole groups of four requests
+    const int4* s4 = (const int4*)a.inst;
+    const int4* c4 = (const int4*)a.cur;
+    const int4* l4 = (const int4*)a.rem;
+
+    int32_t bad = 0;
+    auto check = [&](int s, int cr, int lr) {
+        if (s < 0 || s >= n) bad |= STAR_DEV_BAD_INST;
+        if (cr < 1) bad |= STAR_DEV_BAD_CUR;
+        if (lr < 1) bad |= STAR_DEV_BAD_REM;
+    };
+    // the groups whose validity this workgroup checks; the first are requested now
+    const int v0 = (int)((int64_t)q1 * i / n), v1 = (int)((int64_t)q1 * (i + 1) / n);
+    int4 vs, vc, vl;
+    if (v0 + tid < v1) {
+        vs = s4[v0 + tid];
+        vc = c4[v0 + tid];
+        vl = l4[v0 + tid];
     }
-    if (j < K) pl.tpm[j * pl.sk + i * pl.st] = j > 0 ? hN[j - 1] : INT64_MIN;
-    if (tid == 0) {
-        pl.tpm[K * pl.sk + i * pl.st] = hN[K - 1];
-        pl.tl[K * pl.sk + i * pl.st] = INT64_MIN;
-        pl.tsm[(K - 1) * pl.sk + i * pl.st] = INT64_MIN;
-        pl.tsm[K * pl.sk + i * pl.st] = INT64_MIN;
+    for (int base = 0; base == 0 || base < q1; base += PS_THREADS * PW_RV) {
+        int4 sv[PW_RV];
+#pragma unroll
+        for (int j = 0; j < PW_RV; ++j) {
+            const int q = base + j * PS_THREADS + tid;
+            sv[j] = make_int4(-1, -1, -1, -1);
+            if (q < q1) sv[j] = s4[q];
+        }
+        if (base == 0) {                              // while the first reads are in flight
+            for (int j = tid; j < KP; j += PS_THREADS) {
+                hA[j] = 0;
+                hN[j] = 0;
+                hP[j] = 0;
+            }
+        }
+        if (tid == 0) count = 0;
+        __syncthreads();
+        uint32_t own = 0;
+#pragma unroll
+        for (int j = 0; j < PW_RV; ++j) {
+            own |= (sv[j].x == i ? 1u : 0u) << (4 * j);
+            own |= (sv[j].y == i ? 2u : 0u) << (4 * j);
+            own |= (sv[j].z == i ? 4u : 0u) << (4 * j);
+            own |= (sv[j].w == i ? 8u : 0u) << (4 * j);
+        }
+        const int mine = __builtin_popcount(own);
+        const int incl = wave_incl_add_i32(mine);
+        const int sum = __builtin_amdgcn_readlane(incl, kWave - 1);
+        if (sum > 0) {
+            int at = 0;
+            if ((tid & (kWave - 1)) == 0) at = atomicAdd(&count, sum);
+            at = __builtin_amdgcn_readfirstlane(at) + incl - mine;
+            for (; own; own &= own - 1) {
+                const int bit = __ffs((int)own) - 1;
+                list[at++] = (uint16_t)(((bit >> 2) * PS_THREADS + tid) * 4 + (bit & 3));
+            }
+        }
+        __syncthreads();
+        const int cnt = count;
+        for (int e0 = tid; e0 < cnt; e0 += PS_THREADS * PW_U) {
+            int cr[PW_U], lr[PW_U];
+#pragma unroll
+            for (int u = 0; u < PW_U; ++u) {
+                const int e = e0 + u * PS_THREADS;
+                const int r = 4 * base + list[e < cnt ? e : e0];
+                cr[u] = a.cur[r];
+                lr[u] = a.rem[r];
+            }
+#pragma unroll
+            for (int u = 0; u < PW_U; ++u) {
+                if (e0 + u * PS_THREADS < cnt && cr[u] >= 1 && lr[u] >= 1)
+                    scatter_request(cr[u], lr[u], b, H, alpha0, hA, hN, hP);
+            }
+        }
+        __syncthreads();                              // the list is free
     }
+    for (int r = 4 * q1 + tid; r < a.N; r += PS_THREADS) {
+        const int s = a.inst[r], cr = a.cur[r], lr = a.rem[r];
+        check(s, cr, lr);
+        if (s == i && cr >= 1 && lr >= 1) scatter_request(cr, lr, b, H, alpha0, hA, hN, hP);
+    }
+    for (int q = v0 + tid; q < v1; q += PS_THREADS) {
+        if (q != v0 + tid) {
+            vs = s4[q];
+            vc = c4[q];
+            vl = l4[q];
+        }
+        check(vs.x, vc.x, vl.x);
+        check(vs.y, vc.y, vl.y);
+        check(vs.z, vc.z, vl.z);
+        check(vs.w, vc.w, vl.w);
+    }
+    bad = wave_or_i32(bad);
+    if ((tid & 63) == 0) report_error(a.err_word, bad);
+    __syncthreads();
+    const int q = K - 1 - tid;
+    int64_t xa = 0, xn = 0, xp = 0;
+    if (tid < K) {
+        xa = hA[q + 1];
+        xn = hN[q + 1];
+        xp = hP[q];
+    }
+    finish_curve(a, xa, xn, xp, hA, hN, tmp);
 }
 
 LoadPlan plan_load(const star_load_params& p) {
@@ -387,26 +546,29 @@ hipError_t launch_project_load(const star_load_params& p, const LoadPlan& pl, co
     int32_t* err_word = (int32_t*)(ws + kHdrErrorWord);
     const bool aligned16 = (((uintptr_t)cur | (uintptr_t)rem | (uintptr_t)inst) & 15) == 0;
     if (planes_written) *planes_written = false;
-    // one workgroup per instance, with the curve planes (see project_split_kernel)
-    const bool whole = !pl.split && planes && p.n_buckets <= PS_MAX_K;
-    if ((pl.split || whole) && aligned16) {
+    const bool whole = pl.split && p.n_req <= PW_MAX_REQ &&
+                       p.n_req <= (int64_t)PW_MAX_PER_INST * p.n_inst;
+    // shorter streams: one slice, where the curve planes are wanted
+    const bool shorter = !pl.split && planes && p.n_buckets <= PS_MAX_K;
+    if ((pl.split || shorter) && aligned16) {
         SplitArgs a;
         a.cur = cur; a.rem = rem; a.inst = inst; a.load = load; a.err_word = err_word;
         a.part = (int64_t*)part;
         a.tickets = (uint32_t*)(ws + kHdrTickets);
         a.planes = planes ? *planes : CurvePlanes{};
         if (planes_written) *planes_written = planes != nullptr;
-        a.N = p.n_req; a.n = p.n_inst; a.b = p.bucket; a.K = p.n_buckets; a.KP = pl.kp;
-        a.slices = whole ? 1 : pl.slices;
-        a.slice_len = whole ? p.n_req : pl.slice_len;
-        if (whole) {
-            a.KP = (int)align_up((size_t)p.n_buckets + 1, 2);
+        a.N = p.n_req; a.n = p.n_inst; a.b = p.bucket; a.K = p.n_buckets;
+        a.KP = (int)align_up((size_t)p.n_buckets + 1, 2);
+        a.slices = shorter ? 1 : pl.slices;
+        a.slice_len = shorter ? p.n_req : pl.slice_len;
+        if (whole)
+            hipLaunchKernelGGL(project_whole_kernel, dim3(p.n_inst), dim3(PS_THREADS), 0, stream, a);
+        else if (shorter)
             hipLaunchKernelGGL(project_split_kernel<false>, dim3(p.n_inst), dim3(PS_THREADS), 0,
                                stream, a);
-        } else {
+        else
             hipLaunchKernelGGL(project_split_kernel<true>, dim3(p.n_inst, pl.slices),
                                dim3(PS_THREADS), 0, stream, a);
-        }
         return hipGetLastError();
     }
     const bool vec = p.n_req >= PL_VEC_MIN_REQ && aligned16;

@@ -385,8 +385,6 @@ __device__ inline VKey load_part(VPart* p) {
     return VKey{(s128)(((u128)hi << 64) | (u128)lo), (uint32_t)ix};
 }
 
-// One workgroup: the smallest of `parts` partial keys, written as the move
-// (or the no-move record when none is negative).
 // One workgroup: the smallest of `parts` partial keys, returned to every
 // thread.
 template <bool kAtomic, int kThreads = VS_THREADS>
@@ -438,6 +436,7 @@ __device__ inline star_move move_of(const VKey& m, const int32_t* inst, int n) {
     return mv;
 }
 
+// The same, written as the move (or the no-move record when none is negative).
 template <bool kAtomic>
 __device__ void reduce_parts(VPart* part, int parts, const int32_t* inst, int n, star_move* move,
                              VKey* wbest) {

@@ -74,6 +74,37 @@ def test_projection_with_planes(N, n, b, K, top_k, offset):
     assert rs.ws_score.read_device_error() == ref["flags"]
 
 
+@pytest.mark.parametrize("order", ["blocks", "shuffled", "crowded"])
+@pytest.mark.parametrize("N,n,b,K", [
+    (8192, 4, 3, 40),          # the fewest requests, the most per instance
+    (8193, 960, 1, 1024),      # more instances than a wave's share; a request past the groups
+    (32767, 16, 64, 1024),     # a ragged last group, the most per instance
+    (32768, 64, 100, 333),     # the longest stream
+    (32769, 64, 100, 333),     # one too many: slices that meet
+    (8195, 3, 16, 100),        # ... too many per instance
+])
+def test_projection_one_workgroup_per_instance(N, n, b, K, order):
+    """Streams around the edges of the kernel that packs an instance's own
+    requests, in the orders that fill its list differently, with invalid
+    requests in its first, last and unowned groups."""
+    rng = np.random.default_rng(N + n)
+    cur, rem, inst = synth.random_requests(rng, N, n, cur_hi=5000, len_hi=b * K + 50)
+    inst = (np.arange(N) * n // N).astype(np.int32)
+    if order == "shuffled":
+        rng.shuffle(inst)
+    elif order == "crowded":
+        inst[: N - N // 8] = n // 2        # one list nearly as long as the stream
+    inst[0], cur[1], rem[N - 1], inst[N // 2], cur[N - 6] = -1, 0, -3, n, -7
+    print(f"whole projection N={N} n={n} b={b} K={K} {order}", flush=True)
+    lp = star.load_params(N, n, b, K)
+    ws = star.Workspace(star.project_load_workspace_size(lp))
+    load = torch.full((n, K), -1, dtype=torch.int64, device="cuda")
+    star.project_load(lp, *(torch.from_numpy(a).cuda() for a in (cur, rem, inst)), load, ws)
+    ref, flags = oracle.project_load(cur, rem, inst, n_inst=n, bucket=b, n_buckets=K)
+    assert np.array_equal(load.cpu().numpy(), ref)
+    assert ws.read_device_error() == flags
+
+
 def test_long_output_stress_mix():
     rng = np.random.default_rng(5)
     N, n = 4096, 16
