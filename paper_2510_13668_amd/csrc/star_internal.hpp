@@ -60,6 +60,8 @@ struct LoadPlan {
     int n_chunks = 0;
     bool split = false;  // request slices per instance, met by a last arriver (16-byte
                          // aligned request arrays; otherwise the chunked kernel)
+    bool whole = false;  // split: one workgroup per instance, and slices (0: none) for
+                         // crowded instances
     int slices = 0, slice_len = 0, kp = 0;
     size_t part_bytes = 0;  // the slices' histograms, after the workspace header
 };

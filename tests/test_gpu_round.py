@@ -105,6 +105,74 @@ def test_projection_one_workgroup_per_instance(N, n, b, K, order):
     assert ws.read_device_error() == flags
 
 
+@pytest.mark.parametrize("N,n,b,K,own", [
+    (32768, 64, 64, 1024, 3072),   # the most requests one workgroup takes, three slices idle
+    (32768, 64, 64, 1024, 3073),   # one more: the slices meet
+    (12347, 16, 3, 100, 12347),    # every request, eight slices, a request past the groups
+    (8193, 5, 1, 1023, 8000),      # eight slices, the last one of a request
+    (32768, 85, 100, 50, 32000),   # two slices
+    (32767, 86, 64, 1024, 30000),  # no compute units left for slices
+    (8200, 960, 64, 1024, 8200),   # ... more instances than compute units
+])
+def test_projection_crowded_instance(N, n, b, K, own):
+    """Either side of the line between an instance's one workgroup and the
+    slices that meet, over the slice counts; long sums on popular buckets; the
+    meeting's counters are left at zero; replays repeat the result."""
+    rng = np.random.default_rng(N + n + own)
+    cur, rem, inst = synth.random_requests(rng, N, n, cur_hi=2**31 - 1, len_hi=2 * b)
+    inst = rng.integers(0, n - 1, N).astype(np.int32)      # none on instance n - 1 ...
+    inst[rng.choice(N, own, replace=False)] = n - 1        # ... but these
+    cur[5], rem[N - 1], inst[7] = 0, -3, -1
+    print(f"crowded projection N={N} n={n} b={b} K={K} own={own}", flush=True)
+    lp = star.load_params(N, n, b, K)
+    ws = star.Workspace(star.project_load_workspace_size(lp))
+    load = torch.full((n, K), -1, dtype=torch.int64, device="cuda")
+    dev = [torch.from_numpy(a).cuda() for a in (cur, rem, inst)]
+    ref, flags = oracle.project_load(cur, rem, inst, n_inst=n, bucket=b, n_buckets=K)
+    for _ in range(3):
+        load.fill_(-1)
+        star.project_load(lp, *dev, load, ws)
+        assert np.array_equal(load.cpu().numpy(), ref)
+        assert ws.read_device_error() == flags
+    base = ws.ptr - ws.buf.data_ptr()
+    assert not ws.buf[base:base + star.STAR_WS_HEADER_BYTES].any()
+
+
+def test_projection_crowded_streams_stay_fast():
+    """All requests on one of 16 instances cost at most three times a spread
+    stream's call (1.5 times as measured; 7 times where one workgroup took the
+    whole instance)."""
+    N, n, K = 32768, 16, 1024
+    g = torch.Generator(device="cuda").manual_seed(1)
+    cur = torch.randint(1, K * 32, (N,), device="cuda", dtype=torch.int32, generator=g)
+    u = torch.rand(N, device="cuda", generator=g).clamp(min=1e-6)
+    rem = (64 * u ** (-1 / 1.5)).clamp(1, K * 64).to(torch.int32)
+    lp = star.load_params(N, n, 64, K)
+    ws = star.Workspace(star.project_load_workspace_size(lp))
+    load = torch.empty((n, K), dtype=torch.int64, device="cuda")
+
+    def us(inst):
+        star.project_load(lp, cur, rem, inst, load, ws)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                star.project_load(lp, cur, rem, inst, load, ws)
+        times = []
+        for _ in range(10):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        return min(times)
+
+    spread = us(((torch.arange(N, device="cuda") * n) // N).to(torch.int32))
+    crowded = us(torch.full((N,), 3, dtype=torch.int32, device="cuda"))
+    print(f"spread {spread:.1f} us, crowded {crowded:.1f} us", flush=True)
+    assert crowded < 3 * spread
+
+
 def test_long_output_stress_mix():
     rng = np.random.default_rng(5)
     N, n = 4096, 16
