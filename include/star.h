@@ -235,11 +235,11 @@ typedef struct {
 } star_load_params;
 
 /* The header, plus, for long request streams (n_req >= 8192, n_buckets <=
- * 1024, n_inst <= 960), room for histograms of slices of the requests, which
- * the last workgroup of an instance sums (streams of up to 32768 requests use
- * it for crowded instances alone, and need none past 85 instances); the
- * request arrays are then read in 16-byte groups when all three are 16-byte
- * aligned (other alignments take a kernel that needs no more than the header). */
+ * 1024, n_inst <= 960), per-instance histograms of each request slice that
+ * the last workgroup of the instance sums (up to 32768 requests, of crowded
+ * instances alone); the request arrays are then read in 16-byte groups when
+ * all three are 16-byte aligned (other alignments take a kernel that needs no
+ * more than the header). */
 size_t star_project_load_workspace_size(const star_load_params* p);
 
 star_status star_project_load(const star_load_params* p, const int32_t* cur_len,

@@ -625,6 +625,11 @@ LoadPlan plan_load(const star_load_params& p) {
         const int smax = (int)(p.n_req / PS_MIN_SLICE);
         s = s < smax ? s : smax;
         s = s > 1 ? s : 1;
+        pl.kp = (int)align_up((size_t)p.n_buckets + 1, 2);
+        pl.slice_len = (int)align_up((size_t)ceil_div(p.n_req, s), 4);
+        pl.slices = (int)ceil_div(p.n_req, pl.slice_len);
+        // (the crowded instances' fewer slices of two arrays fit in it too)
+        pl.part_bytes = align_up((size_t)p.n_inst * pl.slices * ps_arrays<false>() * pl.kp * 8, 256);
         if (pl.whole) {
             // the slices that a crowded instance would need, on the compute
             // units that the instances' first workgroups leave: one more
@@ -632,13 +637,9 @@ LoadPlan plan_load(const star_load_params& p) {
             // slices of 64 instances: 8.1 us, not 6.5, at 32768 requests)
             const int left = PS_TARGET_GROUPS / p.n_inst - 1;
             s = s < left ? s : left;
-            if (s < 2) s = 0;
+            pl.slice_len = s < 2 ? p.n_req : (int)align_up((size_t)ceil_div(p.n_req, s), 4);
+            pl.slices = s < 2 ? 0 : (int)ceil_div(p.n_req, pl.slice_len);
         }
-        pl.slice_len = (int)align_up((size_t)ceil_div(p.n_req, s > 0 ? s : 1), 4);
-        pl.slices = s > 0 ? (int)ceil_div(p.n_req, pl.slice_len) : 0;
-        pl.kp = (int)align_up((size_t)p.n_buckets + 1, 2);
-        const size_t arrays = pl.whole ? ps_arrays<true>() : ps_arrays<false>();
-        pl.part_bytes = align_up((size_t)p.n_inst * pl.slices * arrays * pl.kp * 8, 256);
     }
     return pl;
 }
