@@ -146,8 +146,9 @@ star_status star_predict(const star_predict_params* p, const void* hidden, const
  * filled it until its head has run.
  * Errors: STAR_ERR_INVALID_ARG when both sides are NULL or the workspaces
  * overlap; otherwise as star_predict.
- * One launch where the product takes 64 x 64 tiles (bf16) and the head is
- * the 4-row one, else the head and the product as two launches on `stream`.
+ * One launch for bf16 products of 64 x 64 or 128 x 64 tiles, or of 128 x 128
+ * ones that are short or leave room beside them, where the head is the 4-row
+ * one; else the head and the product as two launches on `stream`.
  * ---------------------------------------------------------------------- */
 size_t star_predict_overlap_workspace_size(const star_predict_params* p);
 star_status star_predict_overlap(const star_predict_params* p, const void* hidden_next,

@@ -1623,8 +1623,8 @@ hipError_t launch_predict(const star_predict_params& p, const PredictPlan& pl, c
 
 // ---------------------------------------------------------------------------
 // Two batches in one launch.  Blocks [0, gemm_blocks) compute the next
-// batch's first-layer split-K partials (64 x 64 tiles); the blocks after
-// them run the previous batch's head from its partials.  The roles share no
+// batch's first-layer split-K partials (64 x 64 or 128 x 64 tiles); the blocks
+// after them run the previous batch's head from its partials.  The roles share no
 // data, and each block takes one role for its whole life, so they need no
 // synchronisation.  One launch removes the kernel boundary between the
 // previous batch's head and the next batch's product, and the head's
@@ -1648,12 +1648,11 @@ struct OverlapArgs {
     int B, m, nb, act, ema_init, len_max;
     float ema_alpha;
 };
-// W2 fragments the head role prefetches: 4 keeps the kernel at 90 VGPRs, so
-// head workgroups fit beside the product's two per CU from the start
-// (measured at 1024 x 4096 -> 512 -> 64 bins, per batch: 12.9-13.6 us with
-// 4, 13.4-13.8 with 8 (124 VGPRs), 16.6-17.5 with 16 (214 VGPRs, two
-// workgroups per CU, heads waiting for products to end), against 18.1-18.2
-// for star_predict).
+// W2 fragments the head role loads at a time.  LDS alone sets the workgroups
+// per compute unit (two of 128 x 64, three of 64 x 64), so more fragments would
+// cost no occupancy, but they take longer to request: 8 and 16 were 2.2 and 3.8%
+// slower than 4 over 171 shapes of 128 to 4096 rows with 128 x 64 tiles, 2.8 and
+// 5.7% with 64 x 64 (1024 x 512 x 4096, 128 bins: 14.7, 14.9, 14.9 us per batch).
 constexpr int OV_W2PF = 4;
 
 template <int kS, class SH>
@@ -1695,31 +1694,40 @@ hipError_t launch_predict_overlap(const star_predict_params& p, const PredictPla
     if (p.n_req == 0 || (!hidden_next && !partials_prev)) return hipSuccess;
     const bool bf16 = p.dtype == STAR_BF16;
     const int head_blocks = (int)ceil_div(p.n_req, HD_RB);
-    // Beside the head's workgroups, 64 x 64 tiles that need two workgroups
-    // per CU do worse than half as many 128 x 64 ones (97.0 against 94.6 us
-    // for 8 batches of 1024 x 512 x 4096).  128 x 128 tiles, whose workgroups
-    // are not the head's size, give way to them where the product is short
-    // and both roles fit the chip in two passes (8 batches, two launches
-    // against one: 177 and 143 us at 705 x 440 x 7200, 189 and 176 at 1500 x
-    // 904 x 2000; but 198 and 206 at 2048 x 512 x 4096, 472 and 551 at 1789
-    // x 928 x 7416, where the narrow tiles load half as much again).  The
-    // sums, over the same K-slices in the same order, are the same.
+    // One launch, and its tiles: the product's K-slices are star_predict's, so
+    // the sums are the same over the same slices in the same order whatever the
+    // tile.  128 x 64 tiles, but 64 x 64 ones where those would leave almost half
+    // of the compute units without a product workgroup; 128 x 128 tiles, whose
+    // workgroups are not the head's size, give way only where the product is
+    // short or leaves places for the head (two workgroups of 128 x 64 per compute
+    // unit).  Both lines from 570 shapes of 128 to 4096 rows, us per batch (64 x 64,
+    // 128 x 64, two launches):
+    //   895 x 280 x 3032, 4 slices, 140 wide workgroups: 10.7, 12.9, 15.4
+    //   174 x 808 x 7104, 8 slices, 208: 15.8, 14.1
+    //   1884 x 272 x 1720, 4 slices of 7 steps, 300: 14.6, 15.3, 17.8
+    //   1654 x 256 x 5472, 8 slices of 11 steps, 416: 21.2, 19.4, 21.2
+    //   1789 x 928 x 7416, 2 slices of 58 steps, 420: 75.5, 60.2, 53.7
+    //   3778 x 496 x 2856, 2 slices of 23 steps, 480: 38.6, 36.4, 33.8
+    //   3824 x 424 x 1544, 1 slice of 25 steps, 210: 25.5, 25.3, 31.1
+    constexpr int OV_MIN_WIDE = 140;       // fewer wide workgroups take 64 x 64 tiles
+    constexpr int OV_MAX_WIDE = 384;       // wide workgroups that leave the head its places
+    constexpr int OV_SHORT_STEPS = 19;     // K-steps per slice of a short product
     GemmPlan g = pl.gemm;
-    GemmPlan m = g;
-    m.shape = GemmPlan::kMid;
-    m.tiles_m = (int)ceil_div(p.n_req, G1Mid::BM);
-    m.tiles_n = (int)ceil_div(p.d_hidden, G1Mid::BN);
+    GemmPlan wide = g;
+    wide.shape = GemmPlan::kMid;
+    wide.tiles_m = (int)ceil_div(p.n_req, G1Mid::BM);
+    wide.tiles_n = (int)ceil_div(p.d_hidden, G1Mid::BN);
+    const int64_t wide_blocks = (int64_t)wide.tiles_m * wide.tiles_n * wide.splits;
     const int64_t steps = ceil_div((int64_t)p.d_model * 2, (int64_t)G1Mid::STEP * g.splits);
-    if (bf16 && ((g.shape == GemmPlan::kSmall && g.tiles_m * g.tiles_n * g.splits > 256) ||
-                 (g.shape == GemmPlan::kBig && steps <= 16 &&
-                  (int64_t)m.tiles_m * m.tiles_n * m.splits + head_blocks <= 3 * 256)))
-        g = m;
-    const bool mid = g.shape == GemmPlan::kMid;
-    const size_t lds = mid ? G1Mid::LDS : G1Small::LDS;
-    const bool one = hidden_next && partials_prev && bf16 &&
-                     (mid || g.shape == GemmPlan::kSmall) && !pl.head_tiled &&
-                     pl.head_rows == HD_RB && pl.head_lds <= lds &&
-                     head_blocks <= HD_LOWREG_GROUPS;
+    const bool small = g.shape == GemmPlan::kSmall && wide_blocks <= OV_MIN_WIDE &&
+                       pl.head_lds <= (size_t)G1Small::LDS;
+    const bool narrow = g.shape == GemmPlan::kSmall || g.shape == GemmPlan::kMid ||
+                        (g.shape == GemmPlan::kBig &&
+                         (steps <= OV_SHORT_STEPS || wide_blocks <= OV_MAX_WIDE));
+    const bool one = hidden_next && partials_prev && bf16 && narrow && !pl.head_tiled &&
+                     pl.head_rows == HD_RB && pl.head_lds <= (size_t)G1Mid::LDS;
+    const bool mid = one && !small;
+    if (mid) g = wide;
     if (!one) {          // the two kernels one after the other, same results
         if (partials_prev) {
             const hipError_t e =

@@ -6,6 +6,8 @@ values may land on different integers).  Small shapes are checked row by row
 in full; the full-size workloads are checked on sampled rows (rows are
 independent), in the launch configuration the benchmark uses.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -478,11 +480,17 @@ def test_second_layer_logit_read_through_two_bins(B, d, m, dtype):
 
 @pytest.mark.parametrize("B,d,m,nb,dtype,alpha,steps,same", [
     (1024, 4096, 512, 64, synth.BF16, 0.2, 5, True),   # continuous shape: one launch, 4 K-splits
+    (300, 1024, 256, 64, synth.BF16, 0.2, 3, True),    # 64 x 64 tiles that stay
+    (100, 1024, 2048, 256, synth.BF16, 0.2, 2, True),  # ... but for the head's LDS: 128 x 64
+    (705, 7200, 440, 64, synth.BF16, 0.2, 3, True),    # 128 x 128 tiles that give way, 8 splits
+    (1500, 2000, 904, 64, synth.BF16, 0.2, 3, True),   # ... 2 splits, partial last steps
+    (1325, 5848, 936, 64, synth.BF16, 0.0, 2, True),   # 128 x 64 tiles of the plan
+    (1884, 1720, 272, 64, synth.BF16, 0.2, 3, True),   # 771 workgroups of both roles
     (512, 4096, 512, 64, synth.BF16, 0.0, 3, True),    # one launch, 8 K-splits, no EMA
     (1000, 4040, 400, 64, synth.BF16, 0.2, 3, True),   # one launch, ragged rows, columns and K
     (4096, 5120, 512, 64, synth.BF16, 0.2, 2, True),   # 128 x 128 tiles: two launches
     (64, 1024, 256, 32, synth.F32, 0.2, 3, True),      # fp32: two launches
-    (2100, 4096, 256, 64, synth.BF16, 0.2, 3, True),   # over 512 head workgroups: two launches
+    (2100, 4096, 256, 64, synth.BF16, 0.2, 3, True),   # over 512 head workgroups
     (8192, 3968, 64, 200, synth.BF16, 0.2, 2, True),   # the K-chunked head, 4 planes
     (3000, 136, 72, 20, synth.BF16, 0.2, 3, False),    # one K-slice: star_predict fuses it
     (9000, 512, 1024, 128, synth.BF16, 0.2, 2, False), # one K-slice, the K-chunked head here
@@ -551,3 +559,72 @@ def test_overlap_sequence_equals_predict(B, d, m, nb, dtype, alpha, steps, same)
             if alpha > 0:
                 np.testing.assert_array_equal(ema.cpu().numpy(), want[i][2],
                                               err_msg=f"EMA, batch {i}")
+
+
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p),
+                ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _captured_grids(call):
+    """The grid sizes of the kernels that `call` launches (captured, not run)."""
+    from paper_2510_13668_amd import star
+    hip = star.lib()                      # libstar.so depends on the HIP runtime
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        grids.append(k.grid[0])
+    return grids
+
+
+@pytest.mark.parametrize("B,d,m,nb,plan,tile", [
+    (300, 1024, 256, 64, (64, 64), (64, 64)),
+    (895, 3032, 280, 30, (64, 64), (64, 64)),        # 140 workgroups of 128 x 64 tiles
+    (1024, 4096, 512, 64, (64, 64), (128, 64)),
+    (100, 1024, 2048, 256, (64, 64), (128, 64)),     # the head's LDS
+    (3824, 1544, 424, 64, (64, 64), (128, 64)),      # over 512 head workgroups
+    (1325, 5848, 936, 64, (128, 64), (128, 64)),
+    (1884, 1720, 272, 64, (128, 128), (128, 64)),    # short slices
+    (1654, 5472, 256, 64, (128, 128), (128, 64)),    # ... 416 workgroups of 128 x 64 tiles
+    (3778, 2856, 496, 64, (128, 128), None),         # two launches
+    (8192, 3968, 64, 200, None, None),               # the K-chunked head
+])
+def test_overlap_launches(B, d, m, nb, plan, tile):
+    """What one star_predict_overlap call launches: the product's tiles beside
+    the head in one kernel (tile), or the head and then the product on the
+    plan's own tiles (tile None), which a call without a head always takes."""
+    from paper_2510_13668_amd import star
+    rng = np.random.default_rng(B)
+    f = [synth.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+         for s in ((B, d), (m, d), (nb, m))]
+    pr = Predictor(f[1], f[2], synth.bin_values(nb, 1.0, 1000.0), dtype=synth.BF16,
+                   act=synth.ACT_GELU, n_req=B, len_max=1000)
+    h, p = to_dev(f[0], True), pr.params(False)
+    nbytes = star.predict_overlap_workspace_size(p)
+    splits = (nbytes - star.STAR_WS_HEADER_BYTES) // (B * m * 4)
+    ws = [star.Workspace(nbytes), star.Workspace(nbytes)]
+
+    def call(head):
+        star.predict_overlap(p, h, ws[0], ws[1] if head else None, pr.w1, pr.b1, pr.w2, pr.b2,
+                             pr.bins, None, pr.expected, pr.rem)
+
+    def blocks(t):
+        return -(-B // t[0]) * -(-m // t[1]) * splits
+
+    alone = _captured_grids(lambda: call(False))
+    both = _captured_grids(lambda: call(True))
+    print(f"overlap launches B={B} d={d} m={m}: product {alone}, both {both}", flush=True)
+    if plan:
+        assert alone == [blocks(plan)]
+    head = -(-B // 4)
+    assert both == ([blocks(tile) + head] if tile else [-(-B // 64) if B >= 8192 else head] + alone)
