@@ -19,6 +19,32 @@ from gpu_util import E_TIGHT, Predictor, assert_lengths_close, to_dev, w2_scale
 pytestmark = pytest.mark.gpu
 
 
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p),
+                ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _captured_grids(call):
+    """The grid sizes of the kernels that `call` launches (captured, not run)."""
+    from paper_2510_13668_amd import star
+    hip = star.lib()                      # libstar.so depends on the HIP runtime
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        grids.append(k.grid[0])
+    return grids
+
+
 def _check_rem(rem_gpu, y_ref, len_max):
     ref = np.clip(np.rint(y_ref), 1, len_max)
     assert np.all(np.abs(rem_gpu - ref) <= 0.02 * ref + 1), "rem_len"
@@ -83,7 +109,7 @@ def test_peaky_softmax_bf16():
     # past 512 head workgroups: W2 loaded two fragments at a time
     (synth.BF16, synth.ACT_GELU, 3000, 136, 72, 20),
     (synth.BF16, synth.ACT_RELU, 2049, 264, 2048, 200),
-    # one row tile: 128 x 64 GEMM tiles, ragged rows and columns
+    # one row tile, K-splits, ragged rows and columns
     (synth.BF16, synth.ACT_GELU, 40, 3584, 1096, 20),
     (synth.F32, synth.ACT_GELU, 60, 1028, 1100, 20),
 ])
@@ -124,9 +150,8 @@ def test_wide_head_rows_sampled(B, d, m, nb):
 
 @pytest.mark.gpu
 def test_random_single_row_tile_products():
-    """12 seeded random products of at most 128 rows (one row tile of the
-    first-layer GEMM), where the plan may take 128 x 64 tiles with fewer
-    K-splits (six of these twelve do): ragged rows, width and hidden size,
+    """12 seeded random products of at most 128 rows, one or two row tiles of
+    the first-layer GEMM with K-splits: ragged rows, width and hidden size,
     fp32 and bf16, both activations; every row checked."""
     rng = np.random.default_rng(2510)
     for c in range(12):
@@ -154,10 +179,10 @@ def test_random_single_row_tile_products():
 @pytest.mark.parametrize("B,m", [(1, 64), (64, 72), (65, 64), (129, 136), (700, 504)])
 @pytest.mark.parametrize("kb", [16, 48, 64, 112, 128, 144, 384, 400, 1168])
 def test_ring_edges(dtype, B, m, kb):
-    """The product's ring at its edges: rows of kb bytes of K below one step,
-    whole steps, partial last steps (every split of them included), fewer
-    steps than slots, and rows and columns around the tiles' edges; with bin
-    counts around the head's blocks of 16."""
+    """The product's ring at its edges, with 64 x 64 tiles: rows of kb bytes of
+    K below one step, whole steps, partial last steps (every split of them
+    included), fewer steps than slots, and rows and columns around the tiles'
+    edges; with bin counts around the head's blocks of 16."""
     d = kb // (2 if dtype == synth.BF16 else 4)
     nb = 1 + (B * 7 + kb) % 67
     rng = np.random.default_rng(B + m + kb)
@@ -186,6 +211,52 @@ def test_ring_edges_256_tiles(d):
     print(f"ring 256 tiles d={d}", flush=True)
     _run_case(h, w1, w2, synth.bin_values(nb, 1.0, 32768.0), dtype=synth.BF16,
               act=synth.ACT_RELU, len_max=32768, sample=sample)
+
+
+@pytest.mark.parametrize("dtype,B,m,d,nb,tile,splits", [
+    # 128 x 64: the fused kernel over one step, a partial one, fewer steps than
+    # slots and more; then the two kernels (more bins than the fused one takes)
+    *[(synth.BF16, 8218, 392, d, 20, (128, 64), 1) for d in (64, 72, 128, 192, 200, 328, 400)],
+    (synth.BF16, 6622, 576, 2928, 128, (128, 64), 1),
+    (synth.BF16, 8218, 392, 72, 130, (128, 64), 1),
+    (synth.BF16, 4694, 784, 200, 130, (128, 64), 1),    # ... and the 4-row head
+    (synth.BF16, 7614, 520, 1664, 64, (128, 64), 2),
+    (synth.BF16, 8211, 456, 1648, 20, (128, 64), 2),    # a partial last step
+    (synth.BF16, 8593, 72, 2000, 130, (128, 64), 4),
+    # 128 x 128 likewise
+    *[(synth.BF16, 8218, 200, d, 20, (128, 128), 1) for d in (64, 72, 128, 200, 328)],
+    (synth.BF16, 8218, 200, 328, 130, (128, 128), 1),
+    (synth.BF16, 4521, 72, 1232, 20, (128, 128), 4),
+    (synth.BF16, 705, 440, 7200, 64, (128, 128), 8),
+    # fp32: always two kernels
+    *[(synth.F32, 8218, 72, d, 20, (128, 64), 1) for d in (32, 36, 68, 132)],
+    (synth.F32, 620, 1628, 36, 130, (128, 64), 1),
+    *[(synth.F32, 8144, 456, d, 20, (128, 128), 1) for d in (32, 36, 100)],
+])
+def test_ring_edges_wide_tiles(dtype, B, m, d, nb, tile, splits):
+    """The ring's edges for the 128 x 64 and 128 x 128 tiles, in the fused
+    kernel and in the product of its own, with ragged rows and columns; the
+    captured call's grids show the tile and the K-splits that it takes."""
+    rng = np.random.default_rng(B + m + d)
+    h = rng.standard_normal((B, d)).astype(np.float32)
+    w1 = (rng.standard_normal((m, d)) / np.sqrt(d)).astype(np.float32)
+    w2 = (rng.standard_normal((nb, m)) / np.sqrt(m)).astype(np.float32)
+    b1 = (rng.standard_normal(m) * 0.1).astype(np.float32)
+    if dtype == synth.BF16:
+        h, w1, w2 = (synth.f32_to_bf16_bits(a) for a in (h, w1, w2))
+    bins = synth.bin_values(nb, 1.0, 32768.0)
+    print(f"ring {tile} dtype={dtype} B={B} d={d} m={m} nb={nb}", flush=True)
+    pr = Predictor(w1, w2, bins, dtype=dtype, act=synth.ACT_GELU, b1=b1, n_req=B, len_max=32768)
+    hd = to_dev(h, dtype == synth.BF16)
+    blocks = -(-B // tile[0]) * -(-m // tile[1]) * splits
+    grids = _captured_grids(lambda: pr.run(hd))
+    fused = dtype == synth.BF16 and splits == 1 and nb <= 128
+    tiled = dtype == synth.BF16 and splits <= 4 and B >= 8192
+    assert grids == ([blocks] if fused else [blocks, -(-B // (64 if tiled else 4))])
+    sample = np.unique(np.concatenate([np.arange(130), np.arange(B - 130, B),
+                                       rng.choice(B, 200, replace=False)]))
+    _run_case(h, w1, w2, bins, dtype=dtype, act=synth.ACT_GELU, b1=b1, len_max=32768,
+              sample=sample)
 
 
 def _splits(B, d, m, nb):
@@ -230,8 +301,8 @@ def test_tiled_head_planes_and_activations(B, d, m, nb, act, planes):
 
 
 def test_large_fp32_sampled():
-    """fp32 with 1032 output tiles: the 4-wave 128 x 128 GEMM shape, ragged
-    rows, three K-tiles; checked on sampled rows."""
+    """fp32 with 260 output tiles of 256 x 256, ragged rows, a product of six
+    half-line steps; checked on sampled rows."""
     B, d, m, nb = 16390, 96, 1024, 40
     rng = np.random.default_rng(5)
     h = rng.standard_normal((B, d)).astype(np.float32)
@@ -559,32 +630,6 @@ def test_overlap_sequence_equals_predict(B, d, m, nb, dtype, alpha, steps, same)
             if alpha > 0:
                 np.testing.assert_array_equal(ema.cpu().numpy(), want[i][2],
                                               err_msg=f"EMA, batch {i}")
-
-
-class _KernelNode(ctypes.Structure):
-    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p),
-                ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
-                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
-
-
-def _captured_grids(call):
-    """The grid sizes of the kernels that `call` launches (captured, not run)."""
-    from paper_2510_13668_amd import star
-    hip = star.lib()                      # libstar.so depends on the HIP runtime
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph):
-        call()
-    raw = ctypes.c_void_p(graph.raw_cuda_graph())
-    n = ctypes.c_size_t(0)
-    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
-    nodes = (ctypes.c_void_p * n.value)()
-    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
-    grids = []
-    for node in nodes:
-        k = _KernelNode()
-        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
-        grids.append(k.grid[0])
-    return grids
 
 
 @pytest.mark.parametrize("B,d,m,nb,plan,tile", [
