@@ -6,17 +6,18 @@
 // the continuous-prediction smoothing of Section 4.3 and integerisation.
 //
 // Kernel 1 (gemm1_splitk): Z1 partials = H W1^T over a K-slice, on MFMA
-//   (32x32 blocks), 64 bytes of K per row and step (32 bf16 / 16 fp32)
-//   through a ring of LDS slots filled by direct global-to-LDS loads, split-K
-//   so that small batches still fill the CUs.  Tile shapes: 64x64 and 128x64
+//   (32x32 blocks), 128 bytes of K per row and step (64 bf16 / 32 fp32; half of
+//   it with 256x256 tiles) through a ring of LDS slots filled by direct
+//   global-to-LDS loads, split-K so that small batches still fill the CUs.  Tile shapes: 64x64 and 128x64
 //   on 4 waves, 128x128 and 256x256 on 8 waves; a cost model picks one per
 //   product.  Partials are fp32, reduced later in a fixed order
 //   (deterministic results).
 // Kernel 2 (head): 4 rows per workgroup (many workgroups, so the split-K
-//   partial reads have plenty of loads in flight), 16 for large batches:
-//   fixed-order split-K reduction, bias, activation, the bin GEMM (bf16 MFMA
-//   16x16x32 on a hi/lo split of a1, or fp32 FMA), softmax, expectation,
-//   EMA, round-half-even, clamp.
+//   partial reads have plenty of loads in flight), 64 for large bf16 batches:
+//   fixed-order split-K reduction, bias, activation, the bin GEMM (MFMA
+//   16x16x32 on a bf16 hi/lo split of a1, or 16x16x4 in fp32), softmax,
+//   expectation, EMA, round-half-even, clamp.
+// Both in one (predict_fused): bf16 products of one K-slice, up to 128 bins.
 #include <type_traits>
 
 #include "star_common.hpp"
@@ -407,12 +408,16 @@ constexpr int HD_THREADS = 256;
 // float4 items per thread whose partial loads are in flight together: more
 // when there are few split-K planes (registers hold kS x batch float4)
 template <int kS> constexpr int hd_batch() { return kS == 1 ? 8 : kS == 2 ? 4 : 2; }
-// W2 fragments (16 bins x one K-step) a wave loads at a time, the first group
-// at kernel entry so that its latency overlaps the split-K reads.  A deep group
-// costs registers: past two workgroups per CU (more than 512 of them) the
-// shallow one, which keeps every workgroup resident, is faster (measured:
-// 54.9 -> 50.8 us per call at 4096 rows with two planes; at 1024 rows the
-// deep group is 0.2 us and for the regression head 1.2 us faster).
+// W2 fragments (a bin block x one K-step) a wave loads at a time, the first group
+// at kernel entry so that its latency overlaps the split-K reads.  us per call
+// with 2, 4, 8 and 16:
+//   up to two workgroups per CU (512 of them) the deep group hides the reads of a
+//   wide W2: 300 x 2048 x 4096 fp32, 256 bins 187, 142, 127, 118; 1500 x 1024 x
+//   4096, 128 bins 37.7, 37.6, 37.4, 36.9; narrow ones would do with less: 1024 x
+//   512 x 4096, 64 bins 16.4, 16.4, 16.5, 16.5; 64 rows of it 10.8, 10.7, 11.1, 11.0;
+//   past them, other workgroups hide them and its registers (140 against 80 with
+//   four planes) keep those out: 4096 x 512 x 5120, 64 bins 39.0, 39.6, 41.2, 41.7;
+//   7000 x 256 x 8192 48.3, 48.5, 49.4, 52.5.
 constexpr int HD_W2PF = 16;
 constexpr int HD_W2PF_LOW = 2;
 constexpr int HD_LOWREG_GROUPS = 512;
