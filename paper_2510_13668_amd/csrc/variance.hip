@@ -662,10 +662,11 @@ __global__ __launch_bounds__(VS_THREADS) void var_final_kernel(VPart* part, int 
 // The requests that may move (those on an instance of O) are then packed in
 // LDS, so that the lanes of the waves all score.  Requests are dealt to the
 // workgroups in blocks of 16, because those on one crowded instance are often
-// neighbours.  Measured at 32768 requests on 64 instances, K = 1024: 13.2 us
-// per move, against 18.0 + 10.6 us for the two launches; of it 2.9 us until
-// the move is known, 0.9 classification, 1.1 packing, 3.3 (5.2 in the slowest
-// workgroup) the targets, 1.7 the workgroup's best key.
+// neighbours.  Measured at 32768 requests on 64 instances, K = 1024: 12.5 us
+// per move, against 18.0 + 10.6 us for the two launches (of 13.2 us, before the
+// last request's spare reads went: 2.9 until the move is known, 0.9
+// classification, 1.1 packing, 3.3, 5.2 in the slowest workgroup, the targets,
+// 1.7 the workgroup's best key).
 // ---------------------------------------------------------------------------
 constexpr int PL_THREADS = 512;           // 160 registers a thread: 1024 would spill
 constexpr int PL_WAVES = PL_THREADS / kWave;
@@ -1142,7 +1143,11 @@ __global__ __launch_bounds__(PL_THREADS) void plan_pass_kernel(PlanArgs a) {
         int fj = -1;
         constexpr int SLOTS = PL_WAVES * RPW;
         for (int j0 = wid * RPW; j0 < cnt; j0 += PL_U * SLOTS) {
-            // PL_U requests per lane group, their reads issued together
+            // PL_U requests per lane group, their reads issued together (those
+            // past the last one are not read: with them, plans over many
+            // instances were slower than two launches per move: 8 moves, 20000
+            // requests on one of 900, prep and projection included: 646 us in two
+            // launches each, 709 with, 648 without; on one of 64: 196, 178, 151)
             u128 base[PL_U], dv[PL_U], bp[PL_U];
             uint64_t al[PL_U];
             int64_t need[PL_U];
@@ -1171,7 +1176,8 @@ __global__ __launch_bounds__(PL_THREADS) void plan_pass_kernel(PlanArgs a) {
                 QEntry qe[PL_U][VS_M];
                 int64_t le[PL_U][VS_M];
 #pragma unroll
-                for (int x = 0; x < PL_U; ++x)
+                for (int x = 0; x < PL_U; ++x) {
+                    if (x > 0 && j0 + x * SLOTS >= cnt) break;      // uniform
 #pragma unroll
                     for (int i = 0; i < VS_M; ++i) {
                         const int t = c0 + tl + P * i;
@@ -1179,6 +1185,7 @@ __global__ __launch_bounds__(PL_THREADS) void plan_pass_kernel(PlanArgs a) {
                         qe[x][i] = qt[o];
                         le[x][i] = lt[o];   // row K: unused, there bp is 0
                     }
+                }
 #pragma unroll
                 for (int x = 0; x < PL_U; ++x) {
                     if (j0 + x * SLOTS >= cnt) break;       // uniform
