@@ -1455,8 +1455,6 @@ PredictPlan plan_predict(const star_predict_params& p, bool tiled_ok, bool fused
     PredictPlan pl;
     const GemmPlan g = plan_gemm(p.n_req, p.d_hidden, p.d_model, p.dtype == STAR_BF16 ? 2 : 4);
     pl.gemm = g;
-    pl.tiles_m = g.tiles_m;
-    pl.tiles_n = g.tiles_n;
     const int s = g.splits;
     pl.splits = s;
     if (fused_ok && p.dtype == STAR_BF16 && fused_fits(g, p.n_bins)) {

@@ -49,16 +49,6 @@ __device__ inline void split_bf16x2(float a, float b, uint32_t& hi, uint32_t& lo
 // ---------------------------------------------------------------------------
 // wavefront reductions (64 lanes)
 // ---------------------------------------------------------------------------
-__device__ inline float wave_max_f32(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-__device__ inline float wave_sum_f32(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
 __device__ inline int32_t wave_or_i32(int32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v |= __shfl_xor(v, o, kWave);

@@ -19,7 +19,7 @@ GemmPlan plan_gemm(int M, int N, int K, int elem);
 
 struct PredictPlan {
     GemmPlan gemm;
-    int tiles_m = 0, tiles_n = 0, splits = 1;
+    int splits = 1;
     size_t partial_bytes = 0;   // fp32 split-K partials [splits, B, m]
     size_t head_lds = 0;        // dynamic LDS of the head kernel
     int head_rows = 4;          // rows per head workgroup

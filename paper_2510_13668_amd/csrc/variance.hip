@@ -29,7 +29,7 @@
 //
 // Kernels:
 //  * var_prep_kernel: one workgroup per instance (QA, QB) plus one for the
-//    weight sums (B0, B1, B2); a chunked block scan in LDS.  The
+//    weight sums (B0, B1, B2); a scan by DPP, LDS only across the waves.  The
 //    per-instance tables are stored bucket-major, [k][t] (and a bucket-major
 //    copy of the curves), so that the lanes scoring one request's targets
 //    read one contiguous run.
@@ -158,10 +158,9 @@ __device__ inline void prep_load(const uint16_t* beta, const int64_t* L, bool wr
 }
 
 // The tables of one row, computed by the whole workgroup (sx: the waves'
-// sums in LDS); bb = b^2, and k b^2 < 2^60 (b K <= 2^30).  qt1 and
-// lt1: a second copy of the instance tables, or null.  L is the instance's curve (row < n) or unused
-// (the weights' row, wrow).  A thread reads back only buckets it owns, so
-// a caller may have just written them itself.
+// sums in LDS, used by nothing else); bb = b^2, and k b^2 < 2^60 (b K <=
+// 2^30).  qt1 and lt1: a second copy of the instance tables, or null.  L is the
+// instance's curve (row < n) or unused (the weights' row, wrow).
 __device__ void prep_row(const int64_t* __restrict__ L, const uint16_t* __restrict__ beta, int n,
                          int K, int row, bool wrow, QEntry* __restrict__ qt,
                          int64_t* __restrict__ lt, u128* __restrict__ bs, uint64_t bb,
@@ -171,7 +170,6 @@ __device__ void prep_row(const int64_t* __restrict__ L, const uint16_t* __restri
     const int K1 = K + 1;
     const int per = (K + VP_THREADS - 1) / VP_THREADS;
     const int j0 = min(tid * per, K), j1 = min(j0 + per, K);
-    __syncthreads();   // sx may still be read by a previous row
 
     uint32_t wv[VP_REG];
     int64_t lv[VP_REG];
@@ -387,16 +385,16 @@ __device__ inline VKey load_part(VPart* p) {
 
 // One workgroup: the smallest of `parts` partial keys, returned to every
 // thread.
-template <bool kAtomic, int kThreads = VS_THREADS>
+template <bool kAtomic>
 __device__ VKey reduce_keys(VPart* part, int parts, VKey* wbest) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     constexpr int kBatch = 8;   // partials in flight per thread
     VKey k = no_key();
-    for (int g0 = tid; g0 < parts; g0 += kThreads * kBatch) {
+    for (int g0 = tid; g0 < parts; g0 += VS_THREADS * kBatch) {
         VKey p[kBatch];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
-            const int g = g0 + i * kThreads;
+            const int g = g0 + i * VS_THREADS;
             VPart* src = &part[g < parts ? g : parts - 1];
             if (kAtomic) {
                 p[i] = load_part(src);
@@ -412,7 +410,7 @@ __device__ VKey reduce_keys(VPart* part, int parts, VKey* wbest) {
     if (lane == kWave - 1) wbest[wid] = k;
     __syncthreads();
     VKey m = wbest[0];
-    for (int w = 1; w < kThreads / kWave; ++w) m = vmin(m, wbest[w]);
+    for (int w = 1; w < VS_THREADS / kWave; ++w) m = vmin(m, wbest[w]);
     __syncthreads();
     return m;
 }
