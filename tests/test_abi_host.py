@@ -8,6 +8,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2510_13668_amd import star
 
@@ -304,3 +305,18 @@ def test_read_device_error_rejects_bad_args(L):
     assert L.star_read_device_error(FAKE, None, None) == -1
     assert L.star_read_device_error(None, None, ctypes.byref(code)) == -4
     assert L.star_workspace_init(FAKE, 100, None) == -4
+
+
+def test_current_stream_with_and_without_the_shortcut(monkeypatch):
+    """A call without a stream goes to the current one, also where torch has
+    no raw-stream shortcut; a given stream's handle is taken as it is."""
+    class FakeStream:
+        cuda_stream = 0x1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", FakeStream)
+    monkeypatch.setattr(star, "_raw_current_stream", lambda device: 0x5600 + device)
+    assert star._stream(None) == 0x5603
+    monkeypatch.setattr(star, "_raw_current_stream", None)
+    assert star._stream(None) == 0x1234
+    assert star._stream(FakeStream()) == 0x1234
