@@ -138,6 +138,25 @@ def test_projection_crowded_instance(N, n, b, K, own):
     assert not ws.buf[base:base + star.STAR_WS_HEADER_BYTES].any()
 
 
+@pytest.mark.parametrize("N,n,b,K,top_k", [
+    (9001, 16, 4, 300, 64),     # eight slices
+    (8192, 64, 16, 1024, 256),  # three slices, every thread a bucket
+    (8195, 100, 2, 200, 0),     # one slice
+])
+def test_round_with_a_crowded_instance(N, n, b, K, top_k):
+    """Curves and curve planes from slices that meet, through the scoring."""
+    rng = np.random.default_rng(N + K)
+    cur, rem, inst = synth.random_requests(rng, N, n, cur_hi=5000, len_hi=b * K + 50)
+    inst[: N // 2] = 1
+    inst[2], cur[3], rem[N - 1] = n, 0, -1
+    print(f"crowded round N={N} n={n} b={b} K={K} top_k={top_k}", flush=True)
+    rs = Rescheduler(N, n, b, K, top_k, True, True)
+    rs.run(*(torch.from_numpy(a).cuda() for a in (cur, rem, inst)))
+    ref = oracle.round_(cur, rem, inst, n_inst=n, bucket=b, n_buckets=K, top_k=top_k)
+    assert_round_equal(rs.result(), ref)
+    assert rs.ws_score.read_device_error() == ref["flags"]
+
+
 def test_projection_crowded_streams_stay_fast():
     """All requests on one of 16 instances cost at most three times a spread
     stream's call (1.5 times as measured; 7 times where one workgroup took the
