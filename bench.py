@@ -518,8 +518,8 @@ def bench_plan(args):
                                f"theta 1/10, rem_len > 64",
                    "n_req": N, "n_inst": n, "horizon": wl.horizon, "bucket": b, "max_moves": M,
                    "moves_made": made},
-        "roofline": {"kernel": "star_plan_migrations (prep, then per move a masked scoring pass "
-                               "and a one-workgroup update)",
+        "roofline": {"kernel": "star_plan_migrations (prep, then one launch per move: it "
+                               "executes the last one and scores the next)",
                      "bound": "latency", "achieved": achieved, "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS, "traffic": None,
                      "avg_call_us": call_s * 1e6, "us_per_move": call_s * 1e6 / max(made, 1),

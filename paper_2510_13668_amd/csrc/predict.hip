@@ -1438,8 +1438,9 @@ GemmPlan plan_gemm(int M, int N, int K, int elem) {
 // Products the fused kernel takes: one K-slice (no split-K), a tile shape
 // with an LDS epilogue, at most FU_NB_MAX bins, and a counter per row block
 // in the workspace header.  Measured against the two-kernel path with one
-// slice: 61.1 against 68.3 us at 8192 x 512 x 4096, 62.7 against 73.5 us at
-// 4096 x 1024 x 4096, 37.2 against 41.0 us at 16384 x 256 x 2048.
+// slice (64 bins): 49.5 against 52.7 us at 8192 x 512 x 4096, 48.6 against 60.4
+// at 4096 x 1024 x 4096, 55.0 against 63.5 at 6622 x 576 x 2928, 30.9 against
+// 30.6 at 16384 x 256 x 2048.
 static bool fused_fits(const GemmPlan& g, int nb) {
     if (g.shape != GemmPlan::kSmall && g.shape != GemmPlan::kBig && g.shape != GemmPlan::kMid)
         return false;
